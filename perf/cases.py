@@ -37,7 +37,7 @@ def listed():
         # pair densities of a medium cell at one k-point, many valence bands, 32^3 box
         dict(name="pair-medium-64", kind="pair", n=64, ngw=4000, ng=4000, nk=1, nv=64, nc=128),
         # pair densities of one q with large spheres and odd counts, 48^3 box
-        dict(name="pair-sphere-6000", kind="pair", n=48, ngw=6000, ng=4001, nk=1, nv=32, nc=151),
+        dict(name="pair-sphere-6000", kind="pair", n=48, ngw=6000, ng=5501, nk=1, nv=32, nc=151),
         # static chi sum of the small cell in FP64
         dict(name="chi-fp64-1500", kind="chi", precision="fp64", axis="imag", ng=1500, ng2=0, nk=64, nv=4, nc=400,
              nw=1, emax=0.0),
