@@ -5,7 +5,7 @@ One step = one pass of the whole path over the workload's q points: pair
 densities by FFT for every q -> energy weights + chi-sum for all q and all
 frequencies in one batched call -> epsilon and its inverse per q.  The
 default workload is imaginary-frequency chi0 (64^3 grid, Ng = 4000,
-K = 512,000 pairs, 32 frequencies, split-BF16 chi-sum, FP64 eps^-1): the
+K = 512,000 pairs, 32 frequencies, split (INT8 digit) chi-sum, FP64 eps^-1): the
 largest configuration whose steps fit a run of a few minutes on one GPU.
 The other workloads run in their own precision; the uneven-q one streams
 its 64 q through the GPU in batches whose pair densities fit
@@ -40,8 +40,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
-BF16_PEAK_TFLOPS = 2516.6
-SPLIT_PRODUCTS = 10  # BF16 slice products per FP64-equivalent product in the split form
+INT8_PEAK_TOPS = 5033.2  # dense
+SPLIT_PRODUCTS = 15  # INT8 digit products per FP64-equivalent product in the split form
 
 
 def parse():
@@ -172,7 +172,7 @@ def full_grid_pairs(torch, bgw, n, s, q, cv, cc, M, fft_bytes_nominal, reps=2):
 
 
 def split_vs_fp64(torch, h, bgw, ents, omega, chis64, reps):
-    """Split-BF16 vs FP64 chi-sum over the same resident M (whole batched chi0
+    """Split vs FP64 chi-sum over the same resident M (whole batched chi0
     calls, HIP events on the launch stream), with the relative Frobenius error
     of every split (q, omega) result against the FP64 one (worst reported)."""
     chissp = [torch.empty_like(c) for c in chis64]
@@ -203,7 +203,7 @@ def split_vs_fp64(torch, h, bgw, ents, omega, chis64, reps):
         ng = int(e["M"].shape[1])
         K = int(e["M"].shape[0])
         flops += 4.0 * ng * ng * K * nw
-    issued = SPLIT_PRODUCTS * flops  # BF16 MFMA flops of the split form (ten slice products)
+    issued = SPLIT_PRODUCTS * flops  # INT8 MFMA operations of the split form (fifteen digit products)
     tsp = res["split"][1]
     herk_ms = tsp["split_herk"][0] / reps
     t64 = res["fp64"][0]
@@ -223,8 +223,8 @@ def split_vs_fp64(torch, h, bgw, ents, omega, chis64, reps):
         "fp64_herk_ms": res["fp64"][1]["herk"][0] / reps,
         "split_chi_TFLOPs_fp64_equiv": flops / (tspl * 1e-3) / 1e12,
         "fp64_chi_TFLOPs": flops / (t64 * 1e-3) / 1e12,
-        "split_herk_bf16_TFLOPs": issued / (herk_ms * 1e-3) / 1e12,
-        "split_herk_frac_bf16_peak": issued / (herk_ms * 1e-3) / 1e12 / BF16_PEAK_TFLOPS,
+        "split_herk_int8_TOPs": issued / (herk_ms * 1e-3) / 1e12,
+        "split_herk_frac_int8_peak": issued / (herk_ms * 1e-3) / 1e12 / INT8_PEAK_TOPS,
     }
 
 
@@ -301,7 +301,7 @@ def bench_kx(args, wl):
     if precision == bgw.FP64:
         name, work, peak = "k_herk_f64 (Kx, 4 K^2 Ng)", flops, FP64_PEAK_TFLOPS
     else:
-        name, work, peak = "k_chi_split (Kx, BF16 MFMA, 10 x 4 K^2 Ng)", SPLIT_PRODUCTS * flops, BF16_PEAK_TFLOPS
+        name, work, peak = "k_chi_split (Kx, INT8 MFMA, 15 x 4 K^2 Ng)", SPLIT_PRODUCTS * flops, INT8_PEAK_TOPS
     nl = launches.get(key, 1)
     avg = per_step[key] / nl
     kx_tr = load_traffic(f"herk_{wl.name}", ["paper_1111_4429_amd/csrc/chi.hip", "paper_1111_4429_amd/csrc/common.h"])
@@ -314,7 +314,7 @@ def bench_kx(args, wl):
         "unit": "TFLOP/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f64" if precision == bgw.FP64 else "bf16-split/f32-acc/f64-recombined",
+        "dtype": "f64" if precision == bgw.FP64 else "int8-split/i32-acc/f64-recombined",
         "data": "synthetic (seeded generator: orthonormal plane-wave coefficients, uniform band energies)",
         "config": {"workload": wl.name, "quantity": "Bethe-Salpeter exchange kernel Kx", "grid": f"{n}^3",
                    "ng": ng, "nv": wl.nv, "nc": wl.nc, "nk": wl.nk, "npairs": K,
@@ -654,7 +654,7 @@ def bench_realaxis(args, wl):
     nl = launches[gemm]
     g_ms = per_step[gemm] / nl
     work = SPLIT_PRODUCTS * flops if gemm == "split_herk" else flops
-    peak = BF16_PEAK_TFLOPS if gemm == "split_herk" else FP64_PEAK_TFLOPS
+    peak = INT8_PEAK_TOPS if gemm == "split_herk" else FP64_PEAK_TFLOPS
     ach = work / nl / (g_ms * 1e-3) / 1e12
     src = "split.hip" if gemm == "split_herk" else "chi.hip"
     tr = load_traffic(f"{gemm}_{wl.name}", [f"paper_1111_4429_amd/csrc/{src}", "paper_1111_4429_amd/csrc/common.h"])
@@ -684,7 +684,7 @@ def bench_realaxis(args, wl):
         "unit": "TFLOP/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "bf16-split/f32-acc/f64-recombined" if gemm == "split_herk" else "f64",
+        "dtype": "int8-split/i32-acc/f64-recombined" if gemm == "split_herk" else "f64",
         "data": "synthetic (seeded generator: orthonormal plane-wave coefficients, uniform band energies)",
         "config": {"workload": wl.name, "axis": "retarded", "grid": f"{n}^3", "ng": ng, "nv": nv, "nc": nc, "nk": nk,
                    "npairs": K, "nE": nE, "E_grid": list(REALAXIS_GRID), "broadening_eV": delta,
@@ -696,7 +696,7 @@ def bench_realaxis(args, wl):
                    "eps_inv_TFLOPs": 8.0 * ng ** 3 * nE / (per_step.get("invert", float("nan")) * 1e-3) / 1e12,
                    "eps_inv_path": "pivoted"},
         "split": cmp or None,
-        "roofline": {"kernel": "k_chi_split (BF16 MFMA, 10 x 4 Ng^2 K per weight vector)" if gemm == "split_herk"
+        "roofline": {"kernel": "k_chi_split (INT8 MFMA, 15 x 4 Ng^2 K per weight vector)" if gemm == "split_herk"
                      else "k_herk_f64", "bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
                      "frac": ach / peak, "traffic": None if tr is None else tr["bytes_per_launch"],
                      "algorithmic_per_launch": work / nl, "avg_launch_ms": g_ms, "launches_per_step": nl},
@@ -919,15 +919,15 @@ def main():
         rez = int(np.abs(x["q"]["ge"][:, 2]).max())
         t_bytes += K * 16.0 * b[0] * (2 * rey + 1) * (2 * rez + 1)
     box_bytes = sum(16.0 * b[0] * b[1] * b[2] for b in boxes)
-    split_bf16 = SPLIT_PRODUCTS * chi_flops  # BF16 MFMA flops of the split form: ten products of 4 Ng^2 K
+    split_int8 = SPLIT_PRODUCTS * chi_flops  # INT8 MFMA operations of the split form: fifteen products of 4 Ng^2 K
     work = {
         "pair": ("k_pair_yz (product + z/y FFT)", "hbm", K * box_bytes + t_bytes, "GB/s", HBM_PEAK_GBS),
         "pair_x": ("k_pair_x (x transform + sphere gather)", "hbm", t_bytes + K * 16.0 * sum(ngs), "GB/s",
                    HBM_PEAK_GBS),
         "band": ("k_band_to_real3", "hbm", (nk * (nv + nc)) * box_bytes, "GB/s", HBM_PEAK_GBS),
         "herk": ("k_herk_f64", "mfma", chi_flops, "TFLOP/s", FP64_PEAK_TFLOPS),
-        "split_herk": ("k_chi_split (BF16 MFMA, 10 x 4 Ng^2 K per frequency)", "mfma", split_bf16, "TFLOP/s",
-                       BF16_PEAK_TFLOPS),
+        "split_herk": ("k_chi_split (INT8 MFMA, 15 x 4 Ng^2 K per frequency)", "mfma", split_int8, "TFLOP/s",
+                       INT8_PEAK_TOPS),
         "invert": ("Gauss-Jordan inversion (k_gje_* or k_nsd_*)", "mfma", lu_flops, "TFLOP/s", FP64_PEAK_TFLOPS),
     }
     dominant = max(work, key=lambda k: per_step.get(k, 0))
@@ -960,7 +960,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f64" if precision == bgw.FP64 else "bf16-split/f32-acc/f64-recombined",
+        "dtype": "f64" if precision == bgw.FP64 else "int8-split/i32-acc/f64-recombined",
         "data": "synthetic (seeded generator: orthonormal plane-wave coefficients, uniform band energies)",
         "config": {"workload": wl.name, "grid": f"{n}^3", "transform_box": "x".join(map(str, box)),
                    "ng": ngs[0] if len(ngs) == 1 else ngs, "ngw": len(s["gw"]), "nv": nv, "nc": nc, "nk": nk,

@@ -65,7 +65,8 @@ extern "C" {
 #define BGW_AXIS_ADVANCED 2      /* chi0^a at real frequencies E >= 0 with broadening delta */
 
 #define BGW_FP64 0               /* chi-sum on FP64 MFMA */
-#define BGW_SPLIT_BF16 1         /* chi-sum as split BF16 slices, FP32 accumulation, FP64 recombination */
+#define BGW_SPLIT_BF16 1         /* split chi-sum: 40-bit fixed-point digits on INT8 MFMA, exact INT32 accumulation,
+                                    FP64 recombination (the name is from an earlier BF16 form) */
 
 typedef struct bgw_handle_s *bgw_handle_t;
 
@@ -200,7 +201,7 @@ typedef struct {
  * FP64: one launch for the weights, one persistent rank-K-update launch per
  * output-tile size over every (vector, output tile, K range) work item, one
  * finalize launch.  Split: weights in one launch; the frequency-independent
- * digit slices of every q (k_split_slice); one persistent BF16 launch over
+ * digit slices of every q (k_split_slice); one persistent INT8 launch over
  * every (q, vector, tile, K range) item whose slices fit in the workspace
  * together (usually the whole batch), which slices the weighted side in
  * registers; the FP64 head rows of all vectors of a q in one pass over M;
@@ -295,8 +296,8 @@ int bgw_realify_workspace(bgw_handle_t h, int nk, int nb, int ngw, const double 
  * It is the chi sum with the roles of pairs and G exchanged: M is
  * transposed into the workspace (G becomes the contraction index, the G0
  * row zeroed) and the chi-sum kernels run with the weights v, FP64 or split
- * BF16 as in bgw_chi0.  Kx is Hermitian positive semidefinite for v > 0.
- * The split form scales its digits per run of 96 consecutive G vectors, so a
+ * form as in bgw_chi0.  Kx is Hermitian positive semidefinite for v > 0.
+ * The split form scales its digits per run of 384 consecutive G vectors, so a
  * term orders of magnitude above its neighbours (v(q0+0) ~ 1/q0^2 at small q
  * with head = -1) costs digits of the whole run: leave G = 0 out through
  * `head`, or use FP64, when v has such a term.
@@ -336,7 +337,7 @@ int bgw_bse_kx_workspace(bgw_handle_t h, const bgw_kx_desc *d, size_t *bytes);
  *       S[n][n'] = pf/2 sum_i sum_{G,G'} conj(M[i][n][G]) (einv[G][G'] - delta) v(G') M[i][n'][G']
  * The caller passes the occupied inner states for X and SX, all inner states
  * for CH, and sums the q terms (accumulate).  X runs on the chi-sum kernels
- * (contraction over (i, G), FP64 or split BF16); SX and CH form W M with an
+ * (contraction over (i, G), FP64 or split); SX and CH form W M with an
  * FP64 MFMA product, regroup it by inner state and contract over (i, G).
  * ---------------------------------------------------------------------- */
 #define BGW_SIGMA_X 0
@@ -435,8 +436,8 @@ int bgw_eps_inv_noalloc(bgw_handle_t h, int ng, int nw, const double *vcoul, con
 #define BGW_KERNEL_WEIGHTS 2     /* energy weights */
 #define BGW_KERNEL_HERK 3        /* FP64 chi-sum (rank-K update) */
 #define BGW_KERNEL_FINALIZE 4    /* split reduction, prefactor, Hermitian mirror */
-#define BGW_KERNEL_SPLIT_SLICE 5 /* BF16 slicing of M (split precision) */
-#define BGW_KERNEL_SPLIT_HERK 6  /* BF16 chi-sum with FP64 recombination */
+#define BGW_KERNEL_SPLIT_SLICE 5 /* digit slicing of M (split precision) */
+#define BGW_KERNEL_SPLIT_HERK 6  /* INT8 chi-sum with FP64 recombination */
 #define BGW_KERNEL_HEADWING 7    /* FP64 head/wing row of chi (split precision) */
 #define BGW_KERNEL_EPS_BUILD 8   /* epsilon = 1 - v chi */
 #define BGW_KERNEL_INVERT 9      /* whole epsilon inversion (all panels) */

@@ -24,7 +24,8 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 //                    (1/2) [1/(Delta - E -+ i delta) + 1/(Delta + E +- i delta)],
 //                    with a = Delta - E, b = Delta + E:
 //                    Re = (a / (a^2 + delta^2) + b / (b^2 + delta^2)) / 2,
-//                    Im = +-(delta / (a^2 + delta^2) - delta / (b^2 + delta^2)) / 2.
+//                    Im = +-(delta / (a^2 + delta^2) - delta / (b^2 + delta^2)) / 2
+//                    (the retarded sign; the finalize negates the advanced sum).
 // grid.y: vector; every block strides over that vector's pairs.
 __global__ void k_weights(const WProb *__restrict__ probs) {
     const WProb P = probs[blockIdx.y];
@@ -45,8 +46,7 @@ __global__ void k_weights(const WProb *__restrict__ probs) {
             if (P.kind == kWeightRealRe) {
                 w = 0.5 * (a / da + b / db);
             } else {
-                const double im = 0.5 * (dl / da - dl / db);
-                w = P.kind == kWeightRetIm ? im : -im;
+                w = 0.5 * (dl / da - dl / db);
             }
         }
         P.w[t] = w;
@@ -234,6 +234,7 @@ __global__ void k_chi_finalize(const FinProb *__restrict__ probs) {
         if (P.part_im) {
 #pragma unroll 8
             for (int p = 0; p < P.ns; ++p) b = cadd(b, P.part_im[p * total + src]);
+            if (P.neg_im) b = make_double2(-b.x, -b.y);
         }
         if (!up) {
             a.y = -a.y;

@@ -36,7 +36,7 @@ namespace {
 struct TuneEntry {
     int tile = 64;    // FP64 output tile edge (32 or 64)
     int ipc = 8;      // FP64: target work items per CU when splitting K
-    int nsplit = 0;   // split precision: K splits of the BF16 GEMM (0 = heuristic)
+    int nsplit = 0;   // split precision: K splits of the INT8 GEMM (0 = heuristic)
     double ms = 0.0;  // measured time of the winner
 };
 
@@ -279,8 +279,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
                 wp.nc = q.nc;
                 wp.kind = given ? kWeightGiven
                           : !real_axis ? kWeightImag
-                                     : (part == 0 ? kWeightRealRe
-                                                  : (d->axis == BGW_AXIS_RETARDED ? kWeightRetIm : kWeightAdvIm));
+                                       : (part == 0 ? kWeightRealRe : kWeightRetIm);
                 P.wts.push_back(wp);
                 P.w_off.push_back(off);
                 off += al256(sizeof(double) * (K + 128));  // padded: the split GEMM stages whole 16-pair steps
@@ -362,7 +361,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
             fp.accumulate = d->accumulate;
             fp.skip = -1;
             fp.inplace = P.vpart_off[va] == (size_t)-1 ? 1 : 0;
-            fp.pad = 0;
+            fp.neg_im = d->axis == BGW_AXIS_ADVANCED ? 1 : 0;
             P.fin.push_back(fp);
         }
         long long item0 = 0;
@@ -383,20 +382,24 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
         // ---- split precision: per q the K-split count, the partial sums and the tile walk
         const int vq = d->nw * P.vpq;  // weight vectors per q
         const long long slots = split_grid();
-        long long base_items = 0;
+        long long base_items = 0, wide_items = 0;
         for (int iq = 0; iq < d->nq; ++iq) {
             P.tiles.emplace_back();
             split_tiles(d->q[iq].ng, P.tiles.back());
             base_items += (long long)P.tiles.back().size() * vq;
+            wide_items += split_wide_tiles(d->q[iq].ng) * vq;
         }
-        // K splits per q: the wave-filling rule over the whole batch (or the tuned count)
+        // K splits per q: the wave-filling rule over the whole batch (or the tuned
+        // count), with no more partial sums than tiles a third wider would take: a
+        // workspace limit that fitted those still fits
+        const long long ns_cap = choose_splits(wide_items, slots, 4, 64);
         P.q_ns.assign(d->nq, 1);
         for (int iq = 0; iq < d->nq; ++iq) {
             const bgw_chi_q &q = d->q[iq];
             const TuneEntry e = lookup(s, BGW_SPLIT_BF16, q.ng, q_pairs(q));
             const int nso = force_nsplit ? force_nsplit : e.nsplit;
-            const long long ns = nso > 0 ? nso : choose_splits(base_items, slots, 4, 64);
-            P.q_ns[iq] = (int)std::max<long long>(1, std::min<long long>(ns, split_chunks(q_pairs(q))));
+            const long long ns = nso > 0 ? nso : choose_splits(base_items, slots, 4, ns_cap);
+            P.q_ns[iq] = (int)std::max<long long>(1, std::min(ns, split_max_ns(q_pairs(q))));
         }
         // partial sums per q (none when the raw sums can go straight into chi)
         auto part_bytes = [&](int iq) {
@@ -411,7 +414,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
         size_t hw = 0, ew_all = 0;
         for (int iq = 0; iq < d->nq; ++iq) {
             if (d->q[iq].head >= 0) hw = std::max(hw, sizeof(double2) * (size_t)kHeadSplits * vq * d->q[iq].ng);
-            ew_all += al256((size_t)vq * split_chunks(q_pairs(d->q[iq])) * split_gpad(d->q[iq].ng));
+            ew_all += al256(split_ea_bytes(vq, split_chunks(q_pairs(d->q[iq])), d->q[iq].ng));
         }
         // slice budget: what the device holds next to everything else of the call
         const size_t other = off + al256(hw) + ew_all + ((size_t)2 << 30);
@@ -424,9 +427,11 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
         std::vector<std::pair<int, std::pair<long long, long long>>> ranges;  // (q, [c0, c1))
         for (int iq = 0; iq < d->nq; ++iq) {
             const long long nch = split_chunks(q_pairs(d->q[iq]));
-            const size_t per_chunk = split_slice_bytes(1, d->q[iq].ng);
-            long long fit = std::max<long long>(1, (long long)(budget / per_chunk));
-            if (fit < nch) fit = std::max<long long>(fit, P.q_ns[iq]);  // the first range initialises every split
+            long long fit = nch;
+            if (split_slice_bytes(nch, split_steps(q_pairs(d->q[iq]), 0, nch), d->q[iq].ng) > budget)
+                fit = std::min(nch, std::max<long long>(1, (long long)(budget / split_chunk_bytes(d->q[iq].ng))));
+            // the first range initialises every split
+            if (fit < nch) fit = std::min(nch, std::max(fit, split_min_chunks(P.q_ns[iq])));
             for (long long c0 = 0; c0 < nch; c0 += fit) ranges.push_back({iq, {c0, std::min(nch, c0 + fit)}});
         }
         size_t slice_max = 0, ew_max = 0;
@@ -444,7 +449,8 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
             for (auto &r : ranges) {
                 const int iq = r.first;
                 const long long nchr = r.second.second - r.second.first;
-                const size_t b = al256(split_slice_bytes(nchr, d->q[iq].ng));
+                const size_t b = al256(
+                    split_slice_bytes(nchr, split_steps(q_pairs(d->q[iq]), r.second.first, nchr), d->q[iq].ng));
                 const bool whole = r.second.first == 0 && r.second.second == split_chunks(q_pairs(d->q[iq]));
                 if (!cur.qs.empty() && (!whole || cur_bytes + b > budget)) close();
                 SplitQ e;
@@ -456,7 +462,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
                 cur.sb_off.push_back(cur_bytes);
                 cur.ew_off.push_back(cur_ew);
                 cur_bytes += b;
-                cur_ew += al256((size_t)vq * nchr * split_gpad(d->q[iq].ng));
+                cur_ew += al256(split_ea_bytes(vq, nchr, d->q[iq].ng));
                 if (!whole) close();
                 if (!whole && P.qpart_off[iq] == (size_t)-1) {  // several launches: sums through partials
                     P.qpart_off[iq] = off;
@@ -479,9 +485,10 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
                 e.gpad = split_gpad(q.ng);
                 e.nvec = vq;
                 e.ntiles = (int)P.tiles[iq].size();
-                // every split non-empty; the first range of a q holds >= q_ns chunks, so it
-                // writes all q_ns partial sums that the finalize reads
-                e.ns = std::min<int>(P.q_ns[iq], e.nch);
+                // every split non-empty; the first range of a q holds enough steps for q_ns
+                // splits, so it writes all q_ns partial sums that the finalize reads
+                e.nst = (int)split_steps(e.K, e.chunk0, e.nch);
+                e.ns = (int)std::min<long long>(P.q_ns[iq], split_range_ns(e.nst));
                 e.add = seen[iq] ? 1 : 0;
                 seen[iq] = 1;
                 e.item0 = item0;
@@ -503,7 +510,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
             fp.accumulate = d->accumulate;
             fp.skip = q.head;
             fp.inplace = P.qpart_off[iq] == (size_t)-1 ? 1 : 0;
-            fp.pad = 0;
+            fp.neg_im = d->axis == BGW_AXIS_ADVANCED ? 1 : 0;
             P.fin.push_back(fp);
         }
         P.off_slices = off;
@@ -560,9 +567,10 @@ void bind_plan(const bgw_chi_desc *d, ChiPlan &P, char *ws, char *tab) {
             SplitQ &e = L.qs[i];
             e.w = P.wts[iq * vq].w;
             e.wstride = vq > 1 ? (long long)((P.w_off[iq * vq + 1] - P.w_off[iq * vq]) / sizeof(double)) : 0;
-            e.SB = (const unsigned short *)(ws + P.off_slices + L.sb_off[i]);
-            e.EB = (const int *)(ws + P.off_slices + L.sb_off[i] + split_slices_only_bytes(e.nch, e.ng));
-            e.EA = (const signed char *)(ws + P.off_ew + L.ew_off[i]);
+            e.SB = (const unsigned char *)(ws + P.off_slices + L.sb_off[i]);
+            e.EC = (const int *)((const char *)e.SB + split_slices_only_bytes(e.nst, e.ng));
+            e.EB = (const short *)((const char *)e.EC + split_ec_bytes(e.nst, e.ng));
+            e.EA = (const short *)(ws + P.off_ew + L.ew_off[i]);
             e.out = P.qpart_off[iq] == (size_t)-1 ? (double2 *)q.chi : (double2 *)(ws + P.qpart_off[iq]);
             e.vstride = (long long)(P.qpart_off[iq] == (size_t)-1 ? 1 : P.q_ns[iq]) * q.ng * q.ng;
             e.tiles = (const unsigned *)(tab + P.tiles_off[iq]);
@@ -618,8 +626,8 @@ int enqueue(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, char *ws, char *t
             Timed tm(h, BGW_KERNEL_SPLIT_SLICE, st);
             for (size_t i = 0; i < L.qs.size(); ++i) {
                 const SplitQ &e = L.qs[i];
-                BGW_TRY(launch_split_slices(e.M, e.K, e.ng, e.chunk0, e.nch, (unsigned short *)e.SB, (int *)e.EB, e.w,
-                                            e.wstride, e.nvec, (signed char *)e.EA, st));
+                BGW_TRY(launch_split_slices(e.M, e.K, e.ng, e.chunk0, e.nch, e.nst, (unsigned char *)e.SB, (short *)e.EB, e.w,
+                                            e.wstride, e.nvec, (short *)e.EA, (int *)e.EC, st));
             }
         }
         {
@@ -638,7 +646,8 @@ int enqueue(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, char *ws, char *t
             BGW_TRY(launch_headwing(e.M, e.K, q.ng, q.head, e.w, e.wstride, vq, kHeadSplits, hw, st));
             // the finalize skips row/column head, so these writes may come first
             BGW_TRY(launch_headwing_write(hw, kHeadSplits, vq, q.ng, q.head, q.prefactor, (double2 *)q.chi, d->nw,
-                                          P.vpq == 2 ? 1 : 0, d->accumulate, st));
+                                          P.vpq == 2 ? 1 : 0, d->axis == BGW_AXIS_ADVANCED ? 1 : 0, d->accumulate,
+                                          st));
         }
     }
     Timed tm(h, BGW_KERNEL_FINALIZE, st);

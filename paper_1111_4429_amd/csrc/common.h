@@ -44,6 +44,14 @@ __host__ __device__ inline double2 cadd(double2 a, double2 b) { return make_doub
 __host__ __device__ inline double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __host__ __device__ inline double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
 
+// A pointer read from a device table, as one to global memory: the compiler
+// otherwise emits flat loads and stores, which count against the LDS waits too.
+typedef __attribute__((address_space(1))) double2 global_double2;
+typedef __attribute__((address_space(1))) int global_int;
+__device__ inline const global_double2 *as_global(const double2 *p) { return (const global_double2 *)p; }
+__device__ inline global_double2 *as_global(double2 *p) { return (global_double2 *)p; }
+__device__ inline const global_int *as_global(const int *p) { return (const global_int *)p; }
+
 // ---------------------------------------------------------------- FFT plans
 // One axis of a 3D transform: length n = product of radices (each 2, 3 or 4),
 // twiddle table tw[j] = exp(+2 pi i j / n), j in [0, n), in device memory.
@@ -88,22 +96,25 @@ struct SphereMaps {
 
 // One q of a split-precision chi-sum launch (split.hip), a device table
 // entry.  The launch covers the pair chunks [chunk0, chunk0 + nch) of every
-// entry (96 pairs per chunk) and, per entry, all of its weight vectors.
+// entry (384 pairs, twelve k-steps, per chunk) and, per entry, all of its
+// weight vectors.
 struct SplitQ {
     const double2 *M;          // [K][ng]
     const double *w;           // weight vector v at w + v * wstride, [K] each
-    const unsigned short *SB;  // BF16 digit slices of M for the launch's chunks: [4][nch][6][gpad][32]
-    const int *EB;             // chunk-column exponents of those slices: [nch][gpad]
+    const unsigned char *SB;   // digit slices of M for the launch's chunks: [nch][12][5][gpad][64] bytes
+    const int *EC;             // running sums of their Re digits: [nch][12][5][gpad]
+    const short *EB;           // their chunk-column exponents: [nch][gpad]
     double2 *out;              // raw upper-tile sums of (vector v, K split s): out + v * vstride + s * ng * ng
-    const unsigned *tiles;     // upper tiles (64-row x 128-column) in walk order: I | J << 16
+    const unsigned *tiles;     // upper tiles (64-row x 96-column) in walk order: I | J << 16
     long long K, wstride, vstride;
     long long item0, nitems;   // work items of this entry (nitems a multiple of 8)
     int ng, gpad, nvec, ntiles;
     int chunk0, nch;           // chunk range of the launch
-    int ns;                    // K splits of the chunk range: split s takes chunks [s nch / ns, (s + 1) nch / ns)
+    int nst;                   // its k-steps (32 pairs) that hold pairs < K
+    int ns;                    // K splits: with u = ceil(nst / 2), split s takes the steps 2 [s u / ns, (s + 1) u / ns)
     int add;                   // 1: add to the raw sums already in out (later chunk ranges)
-    int pad[2];
-    const signed char *EA;     // [nvec][nch][gpad] chunk-column exponents of the weighted side
+    int pad;
+    const short *EA;           // [nvec][nch][gpad] chunk-column exponents of the weighted side
 };
 
 // Upper-triangle tile number u -> (ti, tj) in grouped order: bands of four
@@ -192,17 +203,19 @@ struct FinProb {
     int accumulate;
     int skip;      // row/column left untouched (FP64 head row written separately), -1 for none
     int inplace;   // raw upper-triangle sums already sit in chi (ns == 1, no accumulation, no B)
-    int pad;
+    int neg_im;    // 1: chi = pf (A - i B) (advanced: B summed with the retarded weights, so that chi^a is
+                   // chi^r's adjoint to the last bit whatever the sums' rounding)
 };
 
 // Kinds of weight vectors (k_weights), Delta = E_v,k+q - E_c,k < 0, all in hartree:
 //   imaginary axis   w = Delta / (Delta^2 + omega^2)   (omega = 0: static 1 / Delta)
 //   real axis        w = (1/2) [1/(Delta - E -+ i delta) + 1/(Delta + E +- i delta)]
 //                    (upper signs retarded, lower advanced), as its real part and
-//                    its imaginary part, each a real weight vector;
+//                    its imaginary part, each a real weight vector (the advanced
+//                    imaginary part is the retarded one negated: FinProb::neg_im);
 //   given            w = a weight array passed in (the Coulomb factor of the
 //                    Bethe-Salpeter exchange kernel).
-enum WeightKind { kWeightImag = 0, kWeightRealRe = 1, kWeightRetIm = 2, kWeightAdvIm = 3, kWeightGiven = 4 };
+enum WeightKind { kWeightImag = 0, kWeightRealRe = 1, kWeightRetIm = 2, kWeightGiven = 4 };
 
 struct WProb {
     const double *ev;  // [nk][nv] eV (kWeightGiven: the weights themselves, [K])

@@ -1,35 +1,41 @@
 // Split-precision chi sum: chi = pf * X_w^T (X + iY) (real embedding of
-// M^H diag(w) M, see chi.hip) computed from BF16 digit slices on MFMA with
-// FP32 accumulation, recombined in FP64.
+// M^H diag(w) M, see chi.hip) computed from 8-bit digit slices on INT8 MFMA
+// with exact INT32 accumulation, recombined in FP64.
 //
-// Digits.  The real contraction index k' = 2t + part is cut into chunks of
-// 192 (96 pairs, six MFMA k-steps).  Within a chunk every column G of X gets a power-of-two
-// scale 2^eB (eB = exponent of the chunk-column max of |Re M|, |Im M|), and
-// every column of X_w, for each weight vector, the scale 2^eA of the
-// chunk-column max of |w_t Re M|, |w_t Im M| (both found by k_split_slice in
-// its pass over M).  Each scaled value y = x 2^(8-e), |y| < 256, is written
-// as four signed digits in base 512:
-//     y = d1 + d2 2^-9 + d3 2^-18 + d4 2^-27 + r,  |di| <= 256,  |r| <= 2^-28,
-// every digit an integer of magnitude <= 256 and so exact in BF16 (eight
-// significant bits).  The unweighted side's digits do not depend on the
-// frequency: k_split_slice stores them once per q (8 bytes per real value).
-// The weighted side is sliced inside the GEMM from M and w, in registers,
-// for each frequency, so no weighted slices are stored at all.
+// Digits.  The pairs are cut into chunks of 384 (twelve MFMA k-steps of 32).
+// Within a chunk every column G of X gets a power-of-two scale 2^eB (above the
+// chunk-column max of |Re M|, |Im M|), and every column of X_w, for each
+// weight vector, the scale 2^eA above the chunk-column max of |w_t Re M|,
+// |w_t Im M| (both found by k_split_slice in its pass over M).  Each scaled
+// value is rounded once to a 40-bit integer N = rint(x 2^(39-e)) and written as
+// five signed base-256 digits, N = sum_i d_i 256^(4-i), -128 <= d_i <= 127.
+// One FMA with the constant 1.5 2^52 + 0x8080808080 makes all five: the low 40
+// bits of the result's mantissa are N + 0x8080808080, whose bytes are the
+// digits plus 128 (toggling each byte's top bit makes them signed bytes).
+// The unweighted side's digits do not depend on the frequency: k_split_slice
+// stores them once per q (5 bytes per real value).  The weighted side is
+// sliced inside the GEMM from M and w, in registers, for each frequency, so no
+// weighted slices are stored at all.
 //
-// Products (k_chi_split), grouped by weight 2^-9p, one FP32 sum per group:
-//     p = 0: a1 b1                                   (exact: |sum| <= 2^16 * 192 < 2^24)
-//     p = 1: a1 b2 + a2 b1                           (exact while |sum| < 2^24)
-//     p = 2: a1 b3 + a2 b2 + a3 b1
-//            + a1' b4 + a2' b3 + a3' b2 + a4' b1     (rounded at 2^-24 of the group)
-// where ai' = ai 2^-9 (exact in BF16) folds the weight-2^-27 products into
-// the third group.  Ten BF16 MFMA products per (Re, Im); at each chunk end
-// the three FP32 sums are combined in FP64 with the chunk scales
-// 2^(eA + eB - 16) and added to FP64 accumulators.  Terms of weight
-// <= 2^-36 are dropped, and so is the remainder r.  The second group's
-// partial sums pass 2^24 only if most of the chunk's 384 products reach
-// 2^16 with one sign; FP32 then rounds at 2^-24 of that group, 2^-33 of the
-// chunk's leading term.  Expected relative error: a few 1e-11 for positive
-// weights, a few 1e-10 where the weights change sign across a resonance.
+// Re chi takes (Re, Im) of the weighted side against (Re, Im) of the other, Im
+// chi takes (-Im, Re) against the same.  -Im is the bitwise complement of Im's
+// digits: ~d = -d - 1, so the sums come out too small by the sum of the other
+// side's Re digits, which k_split_slice stores as running sums per column
+// (EC) and the chunk end adds back, exactly.
+//
+// Products (k_chi_split): all a_i b_j with i + j = p <= 4, one INT32 sum per
+// p; every sum is exact (|sum| <= 5 2^14 768 < 2^26).  Fifteen INT8 MFMA
+// products per (Re, Im); at each chunk end the five sums are combined in FP64
+// with the chunk scales and added to FP64 accumulators.  Dropped: products of
+// weight 2^-40 of the leading one and below, and the rounding of N (2^-40 of
+// the chunk-column max).  A column with a value that is not finite gets the
+// exponent kNotFinite, which makes its sums NaN.
+//
+// Why INT8: the card's INT8 MFMA has twice the BF16 rate, so fifteen exact
+// 8-bit products cost 3/4 of the ten BF16 products that four 9-bit digits
+// need for a result sixteen times coarser, and cutting a value takes one FMA
+// and about three integer instructions where the BF16 digits took a chain of
+// twelve FP64 operations.
 //
 // The head row/column (G = 0) is recomputed in FP64 from M (k_headwing)
 // because v(q+G) ~ 1/q^2 amplifies it in epsilon.
@@ -40,127 +46,165 @@
 
 namespace bgw {
 
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef int int4_t __attribute__((ext_vector_type(4)));
+typedef int int6_t __attribute__((ext_vector_type(6)));
 
 namespace {
-constexpr int SK = 192;       // real contraction rows per chunk (one set of exponents, FP32 group sums)
-constexpr int SKP = SK / 2;   // pairs per chunk
-constexpr int KS = 32;        // real rows per MFMA k-step (16x16x32)
-constexpr int KSP = KS / 2;   // pairs per k-step
-constexpr int NKS = SK / KS;  // k-steps per chunk
-constexpr int NSL = 4;        // stored slices
-constexpr int NGR = 3;        // FP32 product groups
+constexpr int KSP = 32;       // pairs per MFMA k-step (16x16x64: 64 real rows)
+constexpr int NKS = 12;       // k-steps per chunk
+constexpr int SKP = KSP * NKS; // pairs per chunk (one set of exponents)
+constexpr int UKS = 2;        // K splits are cut at multiples of this many k-steps
+constexpr int KSB = 2 * KSP;  // bytes of one column's digits of one slice and k-step
+constexpr int NSL = 5;        // digits (stored slices of the unweighted side, INT32 product groups)
+constexpr int NCB = 3;        // 16-column blocks of a wave
 constexpr int TR = 64;        // output tile rows: weighted side, sliced in registers
-constexpr int TC = 128;       // output tile columns: unweighted side, digit slices through LDS
+constexpr int TC = 32 * NCB;  // output tile columns: unweighted side, digit slices through LDS
 constexpr int XT = 512;       // GEMM block: 8 waves (two per SIMD), 4 x 2 over the tile
-constexpr int kMinExp = -500; // chunk exponents are clamped here (values below 2^-500 count as zero)
+constexpr int kMinExp = -500; // chunk exponents are clamped here (values below 2^-539 count as zero)
+constexpr int kNotFinite = 0x7fff;  // exponent of a chunk column with a value that is not finite
+constexpr double kFixBias = 6755399441055744.0 + 551911719040.0;  // 1.5 2^52 + 0x8080808080
+constexpr unsigned kToggle = 0x80808080u;
 
 __device__ inline double pow2(int e) { return __longlong_as_double((long long)(e + 1023) << 52); }
 
+// e with mx <= 2^e / 1.005: |N| <= 2^39 / 1.005 + 1 then stays below the
+// largest five-digit value 0x7f7f7f7f7f.
 __device__ inline int chunk_exp(double mx) {
+    if (!(mx <= 1.7e308)) return kNotFinite;
     int e = 0;
-    if (mx > 0.0) (void)frexp(mx, &e);  // mx < 2^e
+    if (mx > 0.0) (void)frexp(mx * 1.005, &e);
     return max(e, kMinExp);
 }
 
-__device__ inline unsigned short bf16_bits_exact(double v) {
-    // v is an integer of at most 9 significant bits: exact in BF16
-    const float f = (float)v;
-    return (unsigned short)(__float_as_uint(f) >> 16);
+// The digits of N = rint(x s) plus 128 in the low 40 bits: lo holds digits 4
+// (low byte) to 1, the low byte of hi digit 0.
+__device__ __forceinline__ void fix40(double x, double s, unsigned &lo, unsigned &hi) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(fma(x, s, kFixBias));
+    lo = (unsigned)b;
+    hi = (unsigned)(b >> 32);
+}
+
+// Digit dwords of four values: d[i] holds digit i of values 0..3 (low byte first).
+__device__ __forceinline__ void digits4(const unsigned (&lo)[4], const unsigned (&hi)[4], unsigned (&d)[NSL]) {
+    const unsigned t0 = __builtin_amdgcn_perm(lo[1], lo[0], 0x05010400u);
+    const unsigned t1 = __builtin_amdgcn_perm(lo[1], lo[0], 0x07030602u);
+    const unsigned u0 = __builtin_amdgcn_perm(lo[3], lo[2], 0x05010400u);
+    const unsigned u1 = __builtin_amdgcn_perm(lo[3], lo[2], 0x07030602u);
+    const unsigned h0 = __builtin_amdgcn_perm(hi[1], hi[0], 0x0c0c0400u);
+    const unsigned h1 = __builtin_amdgcn_perm(hi[3], hi[2], 0x04000c0cu);
+    d[0] = (h0 | h1) ^ kToggle;
+    d[1] = __builtin_amdgcn_perm(u1, t1, 0x07060302u) ^ kToggle;
+    d[2] = __builtin_amdgcn_perm(u1, t1, 0x05040100u) ^ kToggle;
+    d[3] = __builtin_amdgcn_perm(u0, t0, 0x07060302u) ^ kToggle;
+    d[4] = __builtin_amdgcn_perm(u0, t0, 0x05040100u) ^ kToggle;
+}
+
+// max(|re|, |im|), infinity when either is not finite
+__device__ __forceinline__ double abs_max(double2 z) {
+    const double a = fabs(z.x), b = fabs(z.y);
+    return (a <= 1.7e308 && b <= 1.7e308) ? fmax(a, b) : INFINITY;
 }
 }  // namespace
 
 // Digit slices of the unweighted side for chunks [c0, c0 + nchunk) of one q,
 // and the chunk-column exponents of the weighted side of every weight vector.
-// Block = one chunk x 32 columns, 384 threads.  Thread t owns column G = 32
+// Block = one chunk x 32 columns, 768 threads.  Thread t owns column G = 32
 // blockIdx.x + (t/4) % 32 and, in each of the k-steps 2 (t/128) and
-// 2 (t/128) + 1, the four pairs 4 (t%4) .. +3; with this assignment every
+// 2 (t/128) + 1, the eight pairs 8 (t%4) .. +7; with this assignment every
 // 16-byte store instruction of a wave writes 1 KB of contiguous slice memory.
-// S: [NSL][nchunk][NKS][gpad][KS] bf16 bits, each group of 8 values holding four
-// pairs as (Re t0..t3, Im t0..t3); E: [nchunk][gpad] (2^E above the chunk-column
-// max of |Re M|, |Im M|); EA: [nvec][nchunk][gpad], 2^EA above the chunk-column
-// max of |w_v(t) Re M|, |w_v(t) Im M| (clamped to [-128, 127]: a value below
-// 2^-128 only keeps fewer digits).  Pairs >= K are zero.
-constexpr int SLICE_T = 32 * 4 * (NKS / 2);  // 384
+// S: [k-step][NSL][gpad][KSB] bytes, each group of 16 holding eight pairs as
+// (Re t0..t7, Im t0..t7); E: [nchunk][gpad]; EA: [nvec][nchunk][gpad]
+// (chunk_exp of the chunk-column max of |Re M|, |Im M| and of |w_v(t) Re M|,
+// |w_v(t) Im M|).  EC: [k-step][NSL][gpad], entry p the sum of the Re digits 0
+// .. p of the column over the chunk's k-steps up to this one.  Pairs >= K are
+// zero; only the first nst k-steps, those that hold pairs < K, are stored.
+constexpr int SLICE_T = 32 * 4 * (NKS / 2);  // 768
 __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restrict__ M, long long K, int ng, int gpad,
-                                                         long long c0, int nchunk, unsigned short *__restrict__ S,
-                                                         int *__restrict__ E, const double *__restrict__ w,
-                                                         long long wstride, int nvec, signed char *__restrict__ EA) {
+                                                         long long c0, int nchunk, int nst, unsigned char *__restrict__ S,
+                                                         short *__restrict__ E, const double *__restrict__ w,
+                                                         long long wstride, int nvec, short *__restrict__ EA,
+                                                         int *__restrict__ EC) {
     constexpr int NP = 4 * (NKS / 2);  // partial maxima per column
     __shared__ double red[NP][32];
+    __shared__ int dsum[NKS][NSL][32];
     const int q = threadIdx.x & 3, cl = (threadIdx.x >> 2) & 31, kh = threadIdx.x >> 7;
     const int G = blockIdx.x * 32 + cl;
     const int chunk = blockIdx.y;
-    const long long tb = (c0 + chunk) * SKP;
+    const long long tb = (c0 + chunk) * SKP + 2 * kh * KSP + 8 * q;  // k-step i, pair j: tb + KSP i + j
     const bool col = G < ng;
-    double2 m[2][4];  // [k-step i][pair j]
+    double2 m[2][8];  // [k-step i][pair j]
+    double mr[2][8];
     double mx = 0.0;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const long long t = tb + (2 * kh + i) * KSP + 4 * q + j;
+        for (int j = 0; j < 8; ++j) {
+            const long long t = tb + KSP * i + j;
             m[i][j] = (t < K && col) ? M[t * ng + G] : make_double2(0.0, 0.0);
-            mx = fmax(mx, fmax(fabs(m[i][j].x), fabs(m[i][j].y)));
+        }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            mr[i][j] = abs_max(m[i][j]);
+            mx = fmax(mx, mr[i][j]);
         }
     red[4 * kh + q][cl] = mx;
     __syncthreads();
     mx = 0.0;
 #pragma unroll
     for (int k = 0; k < NP; ++k) mx = fmax(mx, red[k][cl]);
-    const size_t slice_stride = (size_t)nchunk * NKS * gpad * KS;
     const int e = chunk_exp(mx);
-    if (q == 0 && kh == 0) E[(size_t)chunk * gpad + G] = e;
-    const double up = pow2(8 - e);
+    if (q == 0 && kh == 0) E[(size_t)chunk * gpad + G] = (short)e;
+    const double up = e == kNotFinite ? 0.0 : pow2(39 - e);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int ks = 2 * kh + i;
-        unsigned short d[NSL][8];
+        unsigned d[4][NSL];  // [Re t0..3, Re t4..7, Im t0..3, Im t4..7]
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int h = 0; h < 2; ++h) {
+            unsigned lo[4], hi[4];
 #pragma unroll
-            for (int part = 0; part < 2; ++part) {
-                const double y = (part ? m[i][j].y : m[i][j].x) * up;
-                const double d1 = rint(y);
-                double r = (y - d1) * 512.0;
-                const double d2 = rint(r);
-                r = (r - d2) * 512.0;
-                const double d3 = rint(r);
-                r = (r - d3) * 512.0;
-                const double d4 = rint(r);
-                const int qq = 4 * part + j;  // real parts first, then imaginary parts
-                d[0][qq] = bf16_bits_exact(d1);
-                d[1][qq] = bf16_bits_exact(d2);
-                d[2][qq] = bf16_bits_exact(d3);
-                d[3][qq] = bf16_bits_exact(d4);
-            }
-        const size_t dst = (((size_t)chunk * NKS + ks) * gpad + G) * KS + 8 * q;
+            for (int j = 0; j < 4; ++j) fix40(m[i][4 * h + j].x, up, lo[j], hi[j]);
+            digits4(lo, hi, d[h]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) fix40(m[i][4 * h + j].y, up, lo[j], hi[j]);
+            digits4(lo, hi, d[2 + h]);
+        }
+        unsigned char *o = S + ((size_t)chunk * NKS + 2 * kh + i) * NSL * gpad * KSB + (size_t)G * KSB + 16 * q;
 #pragma unroll
         for (int sl = 0; sl < NSL; ++sl) {
-            uint4 pk;
-            pk.x = d[sl][0] | ((unsigned)d[sl][1] << 16);
-            pk.y = d[sl][2] | ((unsigned)d[sl][3] << 16);
-            pk.z = d[sl][4] | ((unsigned)d[sl][5] << 16);
-            pk.w = d[sl][6] | ((unsigned)d[sl][7] << 16);
-            *reinterpret_cast<uint4 *>(S + sl * slice_stride + dst) = pk;
+            if (chunk * NKS + 2 * kh + i < nst)
+                *reinterpret_cast<uint4 *>(o + (size_t)(sl * gpad) * KSB) =
+                    make_uint4(d[0][sl], d[1][sl], d[2][sl], d[3][sl]);
+            int t = __builtin_amdgcn_sdot4((int)d[0][sl], 0x01010101, 0, false);
+            t = __builtin_amdgcn_sdot4((int)d[1][sl], 0x01010101, t, false);
+            t += __shfl_xor(t, 1, 64);
+            t += __shfl_xor(t, 2, 64);
+            if (q == 0) dsum[2 * kh + i][sl][cl] = t;
         }
     }
-    // weighted side: the same products fl(w x) the GEMM forms, so 2^EA bounds them
-    double mr[2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mr[i][j] = fmax(fabs(m[i][j].x), fabs(m[i][j].y));
+    __syncthreads();
+    if (threadIdx.x < NSL * 32) {  // one thread per entry and column: running sums over the k-steps
+        const int sl = threadIdx.x >> 5, c = threadIdx.x & 31;
+        int run = 0;
+        for (int ks = 0; ks < min(NKS, nst - chunk * NKS); ++ks) {
+            for (int j = 0; j <= sl; ++j) run += dsum[ks][j][c];
+            EC[(((size_t)chunk * NKS + ks) * NSL + sl) * gpad + blockIdx.x * 32 + c] = run;
+        }
+    }
+    // weighted side: |w| max(|Re M|, |Im M|) bounds the products the GEMM rounds
     for (int v = 0; v < nvec; ++v) {
         const double *wv = w + (size_t)v * wstride;
         double mw = 0.0;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const long long t = tb + (2 * kh + i) * KSP + 4 * q + j;
-                if (t < K) mw = fmax(mw, fabs(wv[t]) * mr[i][j]);
+            for (int j = 0; j < 8; ++j) {
+                const long long t = tb + KSP * i + j;
+                if (t < K && col) {
+                    const double x = fabs(wv[t]) * mr[i][j];
+                    mw = x <= 1.7e308 ? fmax(mw, x) : INFINITY;
+                }
             }
         __syncthreads();  // the previous vector's reduction has been read
         red[4 * kh + q][cl] = mw;
@@ -169,49 +213,40 @@ __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restri
             mw = 0.0;
 #pragma unroll
             for (int k = 0; k < NP; ++k) mw = fmax(mw, red[k][cl]);
-            EA[((size_t)v * nchunk + chunk) * gpad + G] = (signed char)min(127, max(-128, chunk_exp(mw)));
+            EA[((size_t)v * nchunk + chunk) * gpad + G] = (short)chunk_exp(mw);
         }
     }
 }
 
 namespace {
-__device__ inline bf16x8_t as_bf16x8(uint4 u) {
-    bf16x8_t r;
+__device__ __forceinline__ int4_t as_int4(uint4 u) {
+    int4_t r;
     __builtin_memcpy(&r, &u, 16);
     return r;
 }
-// A fragment holds four pairs as (Re t0..t3, Im t0..t3); the Y operand of the
-// imaginary part is (Im t0..t3, -Re t0..t3): the two halves exchanged and the
-// moved real parts negated (sign bits of both BF16 halves of a dword).
-__device__ inline uint4 swap_neg(uint4 u) {
-    uint4 r;
-    r.x = u.z;
-    r.y = u.w;
-    r.z = u.x ^ 0x80008000u;
-    r.w = u.y ^ 0x80008000u;
-    return r;
-}
-#define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16((a), (b), (c), 0, 0, 0)
+#define MFMA(a, b, c) __builtin_amdgcn_mfma_i32_16x16x64_i8((a), (b), (c), 0, 0, 0)
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-// LDS stage of one k-step: the weighted side as FP64 complex, [16 pairs][64
-// columns] (16 B each, 1 KB per pair row); the unweighted side's four digit
-// slices, [slice][128 rows][64 B] with the four 16-B segments of row r stored
+// LDS stage of one k-step: the weighted side as FP64 complex, [32 pairs][64
+// columns] (16 B each, 1 KB per pair row); the unweighted side's five digit
+// slices, [slice][96 rows][64 B] with the four 16-B segments of row r stored
 // in the order seg ^ ((r >> 1) & 3), so that the eight rows one 16-B read
-// phase touches fall in distinct bank groups; the step's 16 weights.
-// Besides the two stages, two exponent buffers hold a
-// chunk's 128 column exponents (int32, bytes 0..511) and 64 row exponents of
-// the weighted side (int8, bytes 512..575): chunk c in buffer c % 2, staged
-// with the chunk's first step and read when the chunk starts and when it ends.
-constexpr int A_LDS = KSP * TR * 16;          // 16 KB
-constexpr int B_SLICE_LDS = TC * KS * 2;      // 8 KB
+// phase touches fall in distinct bank groups; the step's 32 weights.
+// Besides the two stages, two chunk buffers hold a chunk's column exponents
+// (int16, bytes 0..191), 64 row exponents of the weighted side (int16, bytes
+// 256..383) and the digit sums at the item's last k-step in it ([5][96] int32
+// from byte 512 on): chunk c in buffer c % 2, staged with the first step that
+// needs it and read when the chunk starts and when it ends.
+constexpr int A_LDS = KSP * TR * 16;          // 32 KB
+constexpr int B_SLICE_LDS = TC * KSB;         // 6 KB
 constexpr int W_OFF = A_LDS + NSL * B_SLICE_LDS;
-constexpr int STG = W_OFF + 256;              // 48.25 KB
-constexpr int E_LDS = 1024;
+constexpr int STG = W_OFF + 256;              // 62.25 KB
+constexpr int EC_OFF = 512, E_LDS = EC_OFF + NSL * TC * 4;
 constexpr int NWAVE = XT / 64;
-constexpr int PA = KSP / NWAVE;               // 1-KB pieces of the A part per wave: 2
-constexpr int PB = NSL * B_SLICE_LDS / 1024 / NWAVE;  // of the B part: 4
+constexpr int PA = KSP / NWAVE;               // 1-KB pieces of the A part per wave: 4
+constexpr int NB_PIECES = NSL * B_SLICE_LDS / 1024;          // of the B part, all waves: 30
+constexpr int PB = (NB_PIECES + NWAVE - 1) / NWAVE;
 
 // vmcnt(n) alone (expcnt and lgkmcnt left at their maxima); vmcnt is split
 // over bits 3:0 and 15:14 of the immediate
@@ -223,200 +258,191 @@ constexpr int PB = NSL * B_SLICE_LDS / 1024 / NWAVE;  // of the B part: 4
 // flight for later stages.
 __device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Per-lane sources of one item's stage loads.  A piece i of wave w is pair
-// row j = 2w + i of the k-step: lane L loads M[t][G0 + L] (clamped into M;
-// the slicing zeroes what lies outside).  B piece i of wave w is slice w/2,
-// rows 64 (w%2) + 16 i .. +16: lane L loads row 64 (w%2) + 16 i + L/4 at
-// stored segment L%4, i.e. source segment (L%4) ^ ((L/4) & 3), one per-lane
-// address plus i KB.
-// Wave 1 loads the step's weights (lanes 0..7, two each): the weight
-// vectors are padded by 128 entries, and the slicing zeroes pairs past K.
+// Sources of one item's stage loads: wave-uniform bases and offsets (scalar
+// registers) plus one constant lane offset each.
 struct StageSrc {
-    const char *a_base;      // M + G(lane) (bytes), pair rows added per step
-    long long a_row_bytes;   // ng * 16
-    long long kmax;          // last valid pair
-    const char *b_base;      // slice wave/2, row 64 (wave%2) + L/4 and segment of this lane (bytes), k-step added
-    size_t b_step_bytes;     // gpad * KS * 2
-    const double *w;         // weights of this vector
-    const int *eb;           // EB: chunk-column exponents of the slices, [nch][gpad]
-    const signed char *ea;   // EA of this vector: chunk-column exponents of the weighted side, [nch][gpad]
-    int gpad, G0, H0;
+    const char *m;           // M (bytes) at the launch's first pair
+    unsigned m_row;          // ng * 16
+    int m_off;               // lane's column (clamped into M), bytes
+    long long kmax;          // last pair from there on
+    const char *b;           // slices
+    unsigned b_slice;        // bytes of one slice of a k-step: gpad * KSB
+    unsigned b0;             // the tile's first column in it
+    int b_off;               // lane L of a piece: row L/4, source segment (L%4) ^ ((L/8) & 3)
+    const double *w;         // weights of this vector at the launch's first pair
+    const short *eb;         // EB: chunk-column exponents of the slices, [nch][gpad]
+    const short *ea;         // EA of this vector: chunk-column exponents of the weighted side, [nch][gpad]
+    const int *ec;           // EC at the tile's first column
+    int gpad, G0, H0, s1;    // s1: the item's last k-step + 1
 };
 
+// One k-step x into one stage.  A piece i of wave w is pair row 4w + i of the
+// k-step (past K the last pair again: it meets zero digits of the other side);
+// B piece p = w + 8 i is slice p / 6, rows 16 (p % 6) .. +16.  Wave 7 loads the
+// step's weights (lanes 0..15, two each; the vectors are padded by 128 entries)
+// and wave 6 the exponents of the step's chunk when they are new.
 __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, unsigned char *__restrict__ ebuf,
-                                            const StageSrc &S, long long t0, long long step, int wave, int lane) {
+                                            const StageSrc &S, int x, bool first, int wave, int lane) {
+    const long long t0 = (long long)x * KSP;
+    const int rows = (int)min((long long)KSP, S.kmax + 1 - t0);
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(S.m + t0 * S.m_row), 0, (int)(rows * S.m_row), 0x00020000);
 #pragma unroll
-    for (int i = 0; i < PA; ++i) {
-        const long long t = min(t0 + PA * wave + i, S.kmax);
-        __builtin_amdgcn_global_load_lds((const void *)(S.a_base + t * S.a_row_bytes),
-                                         (lds_void_t *)(stage + (PA * wave + i) * 1024), 16, 0, 0);
+    for (int i = 0; i < PA; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t *)(stage + (PA * wave + i) * 1024), 16, S.m_off,
+                                                 (int)(min(PA * wave + i, rows - 1) * S.m_row), 0, 0);
+    const unsigned b_step = NSL * S.b_slice;
+    const __amdgpu_buffer_rsrc_t rb =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(S.b + (size_t)x * b_step), 0, (int)b_step, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+        const int p = wave + NWAVE * i;
+        if ((i + 1) * NWAVE <= NB_PIECES || p < NB_PIECES)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rb, (lds_void_t *)(stage + A_LDS + p * 1024), 16, S.b_off,
+                (int)(S.b0 + (p / (TC / 16)) * S.b_slice + (p % (TC / 16)) * 1024), 0, 0);
     }
-    const char *b = S.b_base + step * S.b_step_bytes;
+    if (wave == NWAVE - 1) {
+        if (lane < 16)
+            __builtin_amdgcn_global_load_lds((const void *)(S.w + t0 + 2 * lane), (lds_void_t *)(stage + W_OFF), 16, 0,
+                                             0);
+    } else if (wave == NWAVE - 2 && (first || x % NKS == 0)) {
+        const long long ch = x / NKS;
+        // 8 exponents per lane; rows past gpad (whose sums are not stored) repeat the last ones
+        if (lane < TC / 8)
+            __builtin_amdgcn_global_load_lds((const void *)(S.eb + ch * S.gpad + S.H0 + 8 * lane), (lds_void_t *)ebuf,
+                                             16, 0, 0);
+        if (lane < TR / 8)
+            __builtin_amdgcn_global_load_lds(
+                (const void *)(S.ea + ch * S.gpad + min(S.G0 + 8 * lane, S.gpad - 8)), (lds_void_t *)(ebuf + 256), 16,
+                0, 0);
+        const long long last = min(S.s1, ((int)ch + 1) * NKS) - 1;
+        if (lane < TC / 4) {
 #pragma unroll
-    for (int i = 0; i < PB; ++i)
-        __builtin_amdgcn_global_load_lds((const void *)(b + i * 1024),
-                                         (lds_void_t *)(stage + A_LDS + (wave >> 1) * B_SLICE_LDS +
-                                                        (wave & 1) * 4096 + i * 1024),
-                                         16, 0, 0);
-    if (wave == 1 && lane < 8)
-        __builtin_amdgcn_global_load_lds((const void *)(S.w + t0 + 2 * lane), (lds_void_t *)(stage + W_OFF), 16, 0,
-                                         0);
-    if (wave == 0 && step % NKS == 0) {
-        const long long ch = step / NKS;
-        const int *er = S.eb + ch * S.gpad;
-        if (lane < 32)
-            __builtin_amdgcn_global_load_lds((const void *)(er + S.H0 + 4 * lane), (lds_void_t *)ebuf, 16, 0, 0);
-        if (lane < 4)
-            __builtin_amdgcn_global_load_lds((const void *)(S.ea + ch * S.gpad + S.G0 + 16 * lane),
-                                             (lds_void_t *)(ebuf + 512), 16, 0, 0);
+            for (int p = 0; p < NSL; ++p)
+                __builtin_amdgcn_global_load_lds((const void *)(S.ec + (last * NSL + p) * S.gpad + 4 * lane),
+                                                 (lds_void_t *)(ebuf + EC_OFF + p * TC * 4), 16, 0, 0);
+        }
     }
 }
-
 
 __device__ __forceinline__ uint4 bfrag(const unsigned char *slice, int row, int lq) {
-    return *reinterpret_cast<const uint4 *>(slice + row * 64 + 16 * (lq ^ ((row >> 1) & 3)));
+    return *reinterpret_cast<const uint4 *>(slice + row * KSB + 16 * (lq ^ ((row >> 1) & 3)));
 }
 
-constexpr int NCB = TC / 32;  // column blocks of a wave (each wave spans 64 of the 128 columns)
-
 struct SplitAcc {
-    float4_t g[NCB][NGR][2];  // [col block][group][re/im]
+    int4_t g[NCB][NSL][2];  // [col block][group][re/im]
     double re[NCB][4], im[NCB][4];
 };
 
-// Digits of two values as the BF16 pairs (low half first) of each slice, and
-// the same digits times 2^-9.
-__device__ __forceinline__ void digits2(double y0, double y1, unsigned (&d)[NSL], unsigned (&ds)[NSL]) {
-    double r0 = y0, r1 = y1;
-#pragma unroll
-    for (int sl = 0; sl < NSL; ++sl) {
-        const double a = rint(r0), b = rint(r1);
-        if (sl + 1 < NSL) {
-            r0 = (r0 - a) * 512.0;
-            r1 = (r1 - b) * 512.0;
-        }
-        const float fa = (float)a, fb = (float)b;
-        d[sl] = __builtin_amdgcn_perm(__float_as_uint(fb), __float_as_uint(fa), 0x07060302u);
-        ds[sl] = __builtin_amdgcn_perm(__float_as_uint(fb * 0.001953125f), __float_as_uint(fa * 0.001953125f),
-                                       0x07060302u);
-    }
-}
+// Digit fragments of this lane's eight pairs y = w_t M_t(G) 2^(39 - eA): per
+// digit six dwords (~Im t0..t7, Re t0..t7, Im t0..t7).  Dwords 2..5 are the
+// operand of Re chi, 0..3 the operand of Im chi, against the same fragment (Re,
+// Im) of the other side.
+struct SplitFrags {
+    int6_t d[NSL];
+};
 
-// The four slice fragments f of this lane's 8 values (Re t0..t3, Im t0..t3)
-// y = w_t M_t(G) 2^(8 - eA), and fs = f times 2^-9.  The values of pairs
-// (t0, t1) are read and sliced before those of (t2, t3).
-__device__ __forceinline__ void slice_frags(const unsigned char *src, const double (&sw)[4], uint4 (&f)[NSL],
-                                            uint4 (&fs)[NSL]) {
-    unsigned d[NSL], ds[NSL];
+__device__ __forceinline__ void slice_frags(const unsigned char *src, const double (&sw)[8], SplitFrags &F) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const double2 m0 = *reinterpret_cast<const double2 *>(src + (2 * h) * 1024);
-        const double2 m1 = *reinterpret_cast<const double2 *>(src + (2 * h + 1) * 1024);
-        digits2(m0.x * sw[2 * h], m1.x * sw[2 * h + 1], d, ds);
+        double2 m[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m[j] = *reinterpret_cast<const double2 *>(src + (4 * h + j) * 1024);
+        unsigned lo[4], hi[4], d[NSL];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fix40(m[j].x, sw[4 * h + j], lo[j], hi[j]);
+        digits4(lo, hi, d);
+#pragma unroll
+        for (int sl = 0; sl < NSL; ++sl) F.d[sl][2 + h] = (int)d[sl];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fix40(m[j].y, sw[4 * h + j], lo[j], hi[j]);
+        digits4(lo, hi, d);
 #pragma unroll
         for (int sl = 0; sl < NSL; ++sl) {
-            if (h == 0) f[sl].x = d[sl], fs[sl].x = ds[sl];
-            else f[sl].y = d[sl], fs[sl].y = ds[sl];
-        }
-        digits2(m0.y * sw[2 * h], m1.y * sw[2 * h + 1], d, ds);
-#pragma unroll
-        for (int sl = 0; sl < NSL; ++sl) {
-            if (h == 0) f[sl].z = d[sl], fs[sl].z = ds[sl];
-            else f[sl].w = d[sl], fs[sl].w = ds[sl];
+            F.d[sl][4 + h] = (int)d[sl];
+            F.d[sl][h] = (int)~d[sl];
         }
     }
 }
 
-// Ten BF16 products per (Re, Im) of the wave's row block and one column block.
-__device__ __forceinline__ void split_mfma(const uint4 (&af)[NSL], const uint4 (&as)[NSL], const uint4 (&bf)[NSL],
-                                           float4_t (&g)[NGR][2]) {
-    const bf16x8_t a1 = as_bf16x8(af[0]), a2 = as_bf16x8(af[1]), a3 = as_bf16x8(af[2]);
-    const bf16x8_t s1 = as_bf16x8(as[0]), s2 = as_bf16x8(as[1]), s3 = as_bf16x8(as[2]), s4 = as_bf16x8(as[3]);
-    const bf16x8_t b1 = as_bf16x8(bf[0]), b2 = as_bf16x8(bf[1]), b3 = as_bf16x8(bf[2]), b4 = as_bf16x8(bf[3]);
-    const bf16x8_t y1 = as_bf16x8(swap_neg(bf[0])), y2 = as_bf16x8(swap_neg(bf[1]));
-    const bf16x8_t y3 = as_bf16x8(swap_neg(bf[2])), y4 = as_bf16x8(swap_neg(bf[3]));
-    g[0][0] = MFMA(a1, b1, g[0][0]);
-    g[0][1] = MFMA(a1, y1, g[0][1]);
-    g[1][0] = MFMA(a1, b2, g[1][0]);
-    g[1][1] = MFMA(a1, y2, g[1][1]);
-    g[1][0] = MFMA(a2, b1, g[1][0]);
-    g[1][1] = MFMA(a2, y1, g[1][1]);
-    g[2][0] = MFMA(a1, b3, g[2][0]);
-    g[2][1] = MFMA(a1, y3, g[2][1]);
-    g[2][0] = MFMA(a2, b2, g[2][0]);
-    g[2][1] = MFMA(a2, y2, g[2][1]);
-    g[2][0] = MFMA(a3, b1, g[2][0]);
-    g[2][1] = MFMA(a3, y1, g[2][1]);
-    g[2][0] = MFMA(s1, b4, g[2][0]);
-    g[2][1] = MFMA(s1, y4, g[2][1]);
-    g[2][0] = MFMA(s2, b3, g[2][0]);
-    g[2][1] = MFMA(s2, y3, g[2][1]);
-    g[2][0] = MFMA(s3, b2, g[2][0]);
-    g[2][1] = MFMA(s3, y2, g[2][1]);
-    g[2][0] = MFMA(s4, b1, g[2][0]);
-    g[2][1] = MFMA(s4, y1, g[2][1]);
+// Fifteen INT8 products per (Re, Im) of the wave's row block and one column block.
+__device__ __forceinline__ void split_mfma(const SplitFrags &A, const uint4 (&bf)[NSL], int4_t (&g)[NSL][2]) {
+#pragma unroll
+    for (int i = 0; i < NSL; ++i)
+#pragma unroll
+        for (int p = i; p < NSL; ++p) {
+            g[p][0] = MFMA(__builtin_shufflevector(A.d[i], A.d[i], 2, 3, 4, 5), as_int4(bf[p - i]), g[p][0]);
+            g[p][1] = MFMA(__builtin_shufflevector(A.d[i], A.d[i], 0, 1, 2, 3), as_int4(bf[p - i]), g[p][1]);
+        }
 }
 
-// Chunk end: the three FP32 groups combined in FP64 with the chunk scales
-// 2^(eA + eB - 16) into the FP64 accumulators.  D layout of 16x16x32: lane
-// l, register r -> row 4 (l/16) + r, col l % 16.  E: the chunk's exponent
-// buffer.
-__device__ __forceinline__ void split_flush(SplitAcc &acc, const int *E, int wave, int li, int lq) {
-    const signed char *Ea = reinterpret_cast<const signed char *>(E) + 512;
-    int era[4];
+// 2^(e - 7), NaN for a column with a value that is not finite
+__device__ __forceinline__ double exp_scale(int e) { return e == kNotFinite ? NAN : pow2(e - 7); }
+
+// Chunk end: the five INT32 groups combined in FP64 with the chunk scales
+// 2^(eA + eB - 14) into the FP64 accumulators.  D layout of 16x16x64: lane
+// l, register r -> row 4 (l/16) + r, col l % 16.  E: the chunk's buffer.
+__device__ __forceinline__ void split_flush(SplitAcc &acc, const unsigned char *E, int wave, int li, int lq) {
+    const short *Eb = reinterpret_cast<const short *>(E);
+    const short *Ea = reinterpret_cast<const short *>(E + 256);
+    double pa[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) era[r] = (int)Ea[16 * (wave >> 1) + 4 * lq + r] - 16;
+    for (int r = 0; r < 4; ++r) pa[r] = exp_scale(Ea[16 * (wave >> 1) + 4 * lq + r]);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
-        const int ec = E[64 * (wave & 1) + 16 * cb + li];
+        const double pb = exp_scale(Eb[16 * NCB * (wave & 1) + 16 * cb + li]);
+        int corr[NSL];
+#pragma unroll
+        for (int p = 0; p < NSL; ++p)
+            corr[p] = reinterpret_cast<const int *>(E + EC_OFF)[p * TC + 16 * NCB * (wave & 1) + 16 * cb + li];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const double sc = pow2(era[r] + ec);
-            const float4_t(&g)[NGR][2] = acc.g[cb];
-            const double vre =
-                (double)g[0][0][r] + ((double)g[1][0][r] + (double)g[2][0][r] * 0.001953125) * 0.001953125;
-            const double vim =
-                (double)g[0][1][r] + ((double)g[1][1][r] + (double)g[2][1][r] * 0.001953125) * 0.001953125;
-            acc.re[cb][r] = fma(vre, sc, acc.re[cb][r]);
-            acc.im[cb][r] = fma(vim, sc, acc.im[cb][r]);
+            double v[2];
+#pragma unroll
+            for (int ri = 0; ri < 2; ++ri) {
+                double x = 0.0;
+#pragma unroll
+                for (int p = NSL - 1; p >= 0; --p)
+                    x = fma(x, 0.00390625, (double)(acc.g[cb][p][ri][r] + (ri ? corr[p] : 0)));
+                v[ri] = x * pa[r];
+            }
+            acc.re[cb][r] = fma(v[0], pb, acc.re[cb][r]);
+            acc.im[cb][r] = fma(v[1], pb, acc.im[cb][r]);
         }
         __builtin_amdgcn_sched_barrier(0);  // one column block at a time
     }
 }
-
-// Upper tiles of the 64-row x 128-column tiling of an ng x ng matrix: tile
-// (I, J) holds some G <= H iff 64 I <= 128 J + 127, i.e. I <= 2 J + 1.
 }  // namespace
 
 // One k-step x: stage step x + 1 into `nxt`, slice this lane's row of the
-// weighted side from `cur`, 80 MFMAs over the four column blocks, then wait
+// weighted side from `cur`, 90 MFMAs over the three column blocks, then wait
 // for step x + 1's loads and meet the block at the barrier.  The two stages
 // are distinct restrict-qualified buffers, so the compiler knows that the
 // loads in flight into one do not alias the reads of the other.
 __device__ __forceinline__ void split_step(const unsigned char *__restrict__ cur, unsigned char *__restrict__ nxt,
-                                           unsigned char *__restrict__ ebuf1, const StageSrc &S, long long x,
-                                           long long s1, long long tbase, long long K, double up, int wave, int lane,
-                                           int li, int lq, SplitAcc &acc) {
+                                           unsigned char *__restrict__ ebuf1, const StageSrc &S, int x, int s1,
+                                           double up, int wave, int lane, int li, int lq, SplitAcc &acc) {
     __builtin_amdgcn_sched_barrier(0);
-    if (x + 1 < s1) stage_issue(nxt, ebuf1, S, tbase + (x + 1) * KSP, x + 1, wave, lane);
+    if (x + 1 < s1) stage_issue(nxt, ebuf1, S, x + 1, false, wave, lane);
     __builtin_amdgcn_sched_barrier(0);
-    // the weighted side of this lane's row, sliced into digits (pairs >= K weigh 0)
-    uint4 af[NSL], as[NSL];
+    // the weighted side of this lane's row, sliced into digits
+    SplitFrags A;
     {
-        const long long tp = tbase + x * KSP + 4 * lq;
-        const double *wl = reinterpret_cast<const double *>(cur + W_OFF) + 4 * lq;
-        double sw[4];
+        const double *wl = reinterpret_cast<const double *>(cur + W_OFF) + 8 * lq;
+        double sw[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sw[j] = tp + j < K ? wl[j] * up : 0.0;
-        slice_frags(cur + (4 * lq) * 1024 + (16 * (wave >> 1) + li) * 16, sw, af, as);
+        for (int j = 0; j < 8; ++j) sw[j] = wl[j] * up;
+        slice_frags(cur + (8 * lq) * 1024 + (16 * (wave >> 1) + li) * 16, sw, A);
     }
     const unsigned char *Bs = cur + A_LDS;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
         uint4 bf[NSL];
 #pragma unroll
-        for (int sl = 0; sl < NSL; ++sl) bf[sl] = bfrag(Bs + sl * B_SLICE_LDS, 64 * (wave & 1) + 16 * cb + li, lq);
-        split_mfma(af, as, bf, acc.g[cb]);
+        for (int sl = 0; sl < NSL; ++sl)
+            bf[sl] = bfrag(Bs + sl * B_SLICE_LDS, 16 * NCB * (wave & 1) + 16 * cb + li, lq);
+        split_mfma(A, bf, acc.g[cb]);
     }
     BGW_WAIT_VM(0);
     stage_barrier();
@@ -432,20 +458,29 @@ __device__ __forceinline__ void split_step(const unsigned char *__restrict__ cur
 // M and the same slices, which their L2 then serves.  With one weight vector
 // the sequence walks the tiles in bands of eight row tiles.
 // Block: 8 waves, two per SIMD; wave w owns rows 16 (w/2) .. +16 and columns
-// 64 (w%2) .. +64 (four column blocks) of the 64 x 128 tile, so each row is
+// 48 (w%2) .. +48 (three column blocks) of the 64 x 96 tile, so each row is
 // sliced by the two waves that share it, and one wave's slicing and LDS
-// reads run under the MFMAs of the other wave on its SIMD.
-// Every k-step (16 pairs) the block stages 16 pair rows of M (the tile's 64
-// columns), the four digit slices of the unweighted side (128 columns) and
-// the 16 weights into LDS with direct global->LDS loads, one step ahead
-// through two stages; each wave slices its 16 rows of w_t M_t(G) into BF16
-// digits in registers and issues 80 MFMAs.
+// reads run under the MFMAs of the other wave on its SIMD.  Three column
+// blocks, not four: 120 INT32 and 48 FP64 accumulators with 30 registers of
+// digit fragments of the weighted side and 20 of the other fit the 256
+// registers of a wave (one wave per SIMD with 512 lost more to the moves
+// between the two halves of its register file).
+// Every k-step (32 pairs) the block stages 32 pair rows of M (the tile's 64
+// columns), the five digit slices of the unweighted side (96 columns) and
+// the 32 weights into LDS with direct global->LDS loads, one step ahead
+// through two stages; each wave slices its 16 rows of w_t M_t(G) into
+// digits in registers and issues 90 MFMAs.
+// What bounds it (Ng = 4000, K = 40 960, four frequencies: 68.4 ms, 2.4 POPS;
+// the BF16 form took 108.4): the MFMAs alone take 42.6 ms, at the 3.7 POPS
+// that the card holds on such data (4.7 on zeros: the clock falls with the
+// power); reading the fragments from LDS adds 7 ms, the barrier 3, the loads
+// into LDS 10 when they hit L2 and 6 more as they miss.
 // out (+)= raw sums (no prefactor) of every element of the tile inside ng x ng.
 __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ qs, int nq, long long i0,
                                                      long long i1) {
     __shared__ __attribute__((aligned(1024))) unsigned char stage0[STG];
     __shared__ __attribute__((aligned(1024))) unsigned char stage1[STG];
-    __shared__ __attribute__((aligned(1024))) unsigned char ebufs[2][E_LDS];
+    __shared__ __attribute__((aligned(512))) unsigned char ebufs[2][E_LDS];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -468,30 +503,26 @@ __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ 
         const long long r0 = u / Q.nvec;
         const int tile = (int)(r0 % Q.ntiles);
         const int split = (int)(r0 / Q.ntiles);
-        const unsigned tw = Q.tiles[tile];
+        const unsigned tw = __builtin_amdgcn_readfirstlane((int)Q.tiles[tile]);  // uniform: scalar addresses
         const int G0 = (int)(tw & 0xffff) * TR, H0 = (int)(tw >> 16) * TC;
-        const int c0 = (int)((long long)split * Q.nch / Q.ns);
-        const int c1 = (int)((long long)(split + 1) * Q.nch / Q.ns);
         const int ng = Q.ng, gpad = Q.gpad;
-        const size_t slice_stride = (size_t)Q.nch * NKS * gpad * KS;
 
         StageSrc S;
-        S.a_base = reinterpret_cast<const char *>(Q.M + min(G0 + lane, ng - 1));
-        S.a_row_bytes = (long long)ng * 16;
-        S.kmax = Q.K - 1;
-        {
-            const int row = 64 * (wave & 1) + (lane >> 2);
-            const int seg = (lane & 3) ^ ((row >> 1) & 3);
-            S.b_base = reinterpret_cast<const char *>(Q.SB + (wave >> 1) * slice_stride) +
-                       ((size_t)(H0 + row) * KS * 2 + seg * 16);
-        }
-        S.b_step_bytes = (size_t)gpad * KS * 2;
-        S.w = Q.w + (size_t)v * Q.wstride;
+        S.m_row = (unsigned)ng * 16;
+        S.m = reinterpret_cast<const char *>(Q.M) + (long long)Q.chunk0 * SKP * S.m_row;
+        S.m_off = min(G0 + lane, ng - 1) * 16;
+        S.kmax = Q.K - 1 - (long long)Q.chunk0 * SKP;
+        S.b = reinterpret_cast<const char *>(Q.SB);
+        S.b_slice = (unsigned)gpad * KSB;
+        S.b0 = (unsigned)H0 * KSB;
+        S.b_off = (lane >> 2) * KSB + 16 * ((lane & 3) ^ ((lane >> 3) & 3));
+        S.w = Q.w + (size_t)v * Q.wstride + (long long)Q.chunk0 * SKP;
         S.eb = Q.EB;
         S.ea = Q.EA + (size_t)v * Q.nch * gpad;
         S.gpad = gpad;
         S.G0 = G0;
         S.H0 = H0;
+        S.ec = Q.EC + H0;
 
         SplitAcc acc;
 #pragma unroll
@@ -499,48 +530,63 @@ __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ 
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc.re[cb][r] = acc.im[cb][r] = 0.0;
 
-        // k-steps [s0, s1) of the launch's chunk range; pair of step x: (chunk0 * 8 + x) * 16
-        const long long s0 = (long long)c0 * NKS, s1 = (long long)c1 * NKS;
-        const long long tbase = (long long)Q.chunk0 * SKP;
-        const long long K = Q.K;
+        // k-steps [s0, s1) of the launch's chunk range, s0 even
+        const int nu = (Q.nst + UKS - 1) / UKS;
+        const int s0 = (int)((long long)split * nu / Q.ns) * UKS;
+        const int s1 = min(Q.nst, (int)((long long)(split + 1) * nu / Q.ns) * UKS);
+        S.s1 = s1;
         const bool in = G0 + 16 * (wave >> 1) + li < ng;  // this lane's slicing row is inside the matrix
 
-        stage_issue(stage0, ebufs[c0 & 1], S, tbase + s0 * KSP, s0, wave, lane);
+        stage_issue(stage0, ebufs[(s0 / NKS) & 1], S, s0, true, wave, lane);
         BGW_WAIT_VM(0);
         stage_barrier();
 
-        for (int ch = c0; ch < c1; ++ch) {
-            const int *E = reinterpret_cast<const int *>(ebufs[ch & 1]);
+        for (int xc = s0; xc < s1;) {  // one chunk, or the item's part of it
+            const int ch = xc / NKS;
+            const int xe = min(s1, (ch + 1) * NKS);
+            const unsigned char *E = ebufs[ch & 1];
             unsigned char *En = ebufs[(ch + 1) & 1];
-            // slicing scale of this lane's row: 2^(8 - eA)
-            const double up =
-                in ? pow2(8 - (int)reinterpret_cast<const signed char *>(E)[512 + 16 * (wave >> 1) + li]) : 0.0;
+            // slicing scale of this lane's row: 2^(39 - eA)
+            const int ea = reinterpret_cast<const short *>(E + 256)[16 * (wave >> 1) + li];
+            const double up = in && ea != kNotFinite ? pow2(39 - ea) : 0.0;
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-                for (int p = 0; p < NGR; ++p)
+                for (int p = 0; p < NSL; ++p)
 #pragma unroll
-                    for (int ri = 0; ri < 2; ++ri) acc.g[cb][p][ri] = (float4_t){0.f, 0.f, 0.f, 0.f};
-            const long long xb = (long long)ch * NKS;  // even: step xb uses stage0
+                    for (int ri = 0; ri < 2; ++ri) acc.g[cb][p][ri] = (int4_t){0, 0, 0, 0};
+            if (xc % NKS) {  // the item starts inside the chunk: the digit sums before it do not belong
+                const global_int *c0 = as_global(S.ec + (size_t)(xc - 1) * NSL * gpad + 16 * NCB * (wave & 1) + li);
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+                    for (int p = 0; p < NSL; ++p) {
+                        const int c = -c0[p * gpad + 16 * cb];
+                        acc.g[cb][p][1] = (int4_t){c, c, c, c};
+                    }
+            }
 #pragma unroll 1
-            for (int ks = 0; ks < NKS; ks += 2) {
-                split_step(stage0, stage1, En, S, xb + ks, s1, tbase, K, up, wave, lane, li, lq, acc);
-                split_step(stage1, stage0, En, S, xb + ks + 1, s1, tbase, K, up, wave, lane, li, lq, acc);
+            for (int x = xc; x < xe; x += 2) {  // xc is even: step x uses stage0
+                split_step(stage0, stage1, En, S, x, s1, up, wave, lane, li, lq, acc);
+                if (x + 1 < xe) split_step(stage1, stage0, En, S, x + 1, s1, up, wave, lane, li, lq, acc);
             }
             split_flush(acc, E, wave, li, lq);
+            xc = xe;
         }
 
-        double2 *o = Q.out + (size_t)v * Q.vstride + (size_t)split * ng * ng;
+        global_double2 *o = as_global(Q.out + (size_t)v * Q.vstride + (size_t)split * ng * ng);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int G = G0 + 16 * (wave >> 1) + 4 * lq + r;
-                const int H = H0 + 64 * (wave & 1) + 16 * cb + li;
+                const int H = H0 + 16 * NCB * (wave & 1) + 16 * cb + li;
                 if (G < ng && H < ng) {
-                    double2 val = make_double2(acc.re[cb][r], acc.im[cb][r]);
-                    if (Q.add) val = cadd(val, o[(size_t)G * ng + H]);
-                    o[(size_t)G * ng + H] = val;
+                    global_double2 &e = o[(size_t)G * ng + H];
+                    double re = acc.re[cb][r], im = acc.im[cb][r];
+                    if (Q.add) re += e.x, im += e.y;
+                    e.x = re;
+                    e.y = im;
                 }
             }
         __syncthreads();  // the stages and exponent buffers are reused by the block's next item
@@ -595,10 +641,10 @@ __global__ __launch_bounds__(256) void k_headwing(const double2 *__restrict__ M,
 // Row and column `head` of every output matrix of one q: with A from vector
 // va and (real frequency axis) B from vector vb = va + 1,
 // chi[head][H] (+)= pf (A_H + i B_H), chi[H][head] (+)= pf (conj A_H + i conj B_H),
-// where A_H = sum_s hw[s][va][H]; without B, chi is Hermitian and its head
+// where A_H = sum_s hw[s][va][H] (B negated with neg_im); without B, chi is Hermitian and its head
 // diagonal exactly real.  grid: (ng / 256, output matrices).
 __global__ void k_headwing_write(const double2 *__restrict__ hw, int nsplit, int nvec, int ng, int head, double pf,
-                                 double2 *__restrict__ chi, int two, int accumulate) {
+                                 double2 *__restrict__ chi, int two, int neg_im, int accumulate) {
     const int H = blockIdx.x * blockDim.x + threadIdx.x;
     if (H >= ng) return;
     const int f = blockIdx.y;
@@ -607,6 +653,7 @@ __global__ void k_headwing_write(const double2 *__restrict__ hw, int nsplit, int
     for (int p = 0; p < nsplit; ++p) a = cadd(a, hw[((size_t)p * nvec + va) * ng + H]);
     if (two)
         for (int p = 0; p < nsplit; ++p) b = cadd(b, hw[((size_t)p * nvec + va + 1) * ng + H]);
+    if (neg_im) b = make_double2(-b.x, -b.y);
     if (H == head) {
         a.y = 0.0;
         b.y = 0.0;
@@ -644,30 +691,57 @@ int split_gpad(int ng) { return (ng + TC - 1) / TC * TC; }
 
 long long split_chunks(long long K) { return (K + SKP - 1) / SKP; }
 
-size_t split_slices_only_bytes(long long nch, int ng) { return (size_t)nch * NSL * SK * split_gpad(ng) * 2; }
-
-size_t split_slice_bytes(long long nch, int ng) {
-    return split_slices_only_bytes(nch, ng) + sizeof(int) * (size_t)nch * split_gpad(ng);
+long long split_steps(long long K, long long chunk0, long long nch) {
+    return std::min(nch * NKS, (K - chunk0 * SKP + KSP - 1) / KSP);
 }
 
-// Upper tiles in walk order: bands of eight row tiles, each band walked
-// column tile by column tile.
+// A split keeps at least three k-steps (96 pairs): its partial sums cost as much
+// as they save below that.
+long long split_max_ns(long long K) { return (K + 3 * KSP - 1) / (3 * KSP); }
+
+long long split_range_ns(long long nst) { return (nst + UKS - 1) / UKS; }
+
+long long split_min_chunks(long long ns) { return (ns * UKS + NKS - 1) / NKS; }
+
+size_t split_slices_only_bytes(long long nst, int ng) { return (size_t)nst * NSL * KSB * split_gpad(ng); }
+
+size_t split_ec_bytes(long long nst, int ng) { return sizeof(int) * (size_t)nst * NSL * split_gpad(ng); }
+
+size_t split_slice_bytes(long long nch, long long nst, int ng) {
+    return split_slices_only_bytes(nst, ng) + split_ec_bytes(nst, ng) + sizeof(short) * (size_t)nch * split_gpad(ng);
+}
+
+size_t split_chunk_bytes(int ng) { return split_slice_bytes(1, NKS, ng); }
+
+size_t split_ea_bytes(long long nvec, long long nch, int ng) {
+    return sizeof(short) * (size_t)nvec * nch * split_gpad(ng);
+}
+
+// Upper tiles (those with some G <= H) in walk order: bands of eight row
+// tiles, each band walked column tile by column tile.
 void split_tiles(int ng, std::vector<unsigned> &out) {
     const int nti = (ng + TR - 1) / TR, ntj = (ng + TC - 1) / TC;
     out.clear();
     for (int b0 = 0; b0 < nti; b0 += 8)
         for (int J = 0; J < ntj; ++J)
             for (int I = b0; I < std::min(nti, b0 + 8); ++I)
-                if (I <= 2 * J + 1) out.push_back((unsigned)I | ((unsigned)J << 16));
+                if (TR * I <= TC * J + TC - 1) out.push_back((unsigned)I | ((unsigned)J << 16));
+}
+
+long long split_wide_tiles(int ng) {
+    const int nti = (ng + TR - 1) / TR, ntj = (ng + 127) / 128;
+    long long n = 0;
+    for (int I = 0; I < nti; ++I) n += ntj - I / 2;  // those with 64 I <= 128 J + 127
+    return n;
 }
 
 int split_grid() { return device_cus() / 8 * 8; }
 
-int launch_split_slices(const double2 *M, long long K, int ng, long long c0, int nch, unsigned short *S, int *E,
-                        const double *w, long long wstride, int nvec, signed char *EA, hipStream_t st) {
+int launch_split_slices(const double2 *M, long long K, int ng, long long c0, int nch, int nst, unsigned char *S,
+                        short *E, const double *w, long long wstride, int nvec, short *EA, int *EC, hipStream_t st) {
     const int gpad = split_gpad(ng);
-    hipLaunchKernelGGL(k_split_slice, dim3(gpad / 32, nch), dim3(SLICE_T), 0, st, M, K, ng, gpad, c0, nch, S, E, w,
-                       wstride, nvec, EA);
+    hipLaunchKernelGGL(k_split_slice, dim3(gpad / 32, nch), dim3(SLICE_T), 0, st, M, K, ng, gpad, c0, nch, nst, S, E, w,
+                       wstride, nvec, EA, EC);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
@@ -693,9 +767,9 @@ int launch_headwing(const double2 *M, long long K, int ng, int head, const doubl
 }
 
 int launch_headwing_write(const double2 *hw, int nsplit, int nvec, int ng, int head, double pf, double2 *chi, int nout,
-                          int two, int accumulate, hipStream_t st) {
+                          int two, int neg_im, int accumulate, hipStream_t st) {
     hipLaunchKernelGGL(k_headwing_write, dim3((ng + 255) / 256, nout), dim3(256), 0, st, hw, nsplit, nvec, ng, head,
-                       pf, chi, two, accumulate);
+                       pf, chi, two, neg_im, accumulate);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
