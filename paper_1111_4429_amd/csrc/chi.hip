@@ -13,10 +13,9 @@
 #include <algorithm>
 
 #include "common.h"
+#include "f64_tile.h"
 
 namespace bgw {
-
-typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // Energy weights of one vector, Delta_t = (E_v,k+q - E_c,k) / Ha (see WeightKind):
 //   imaginary axis:  w = Delta / (Delta^2 + omega^2)
@@ -54,175 +53,22 @@ __global__ void k_weights(const WProb *__restrict__ probs) {
 }
 
 namespace {
-constexpr int KC = 8;  // complex pairs per LDS stage
-
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-// Two LDS stages of a T-column tile: [stage][P, Q][KC pairs][T columns] complex.
-template <int T>
-struct PqLds {
-    __attribute__((aligned(1024))) unsigned char b[2][2][KC * T * 16];
-};
-
-// What one block loads: wave w takes the four pair rows 4 (w % 2) .. +3 of P (w
-// < 2) or of Q.
-struct PqSrc {
-    const double2 *base;  // the operand at the tile's first column
-    long long ld;
-    int bytes;            // of a row from there on, at most T columns
-    const double *w;
-};
-
-// Workgroup barrier: this wave's loads have landed, the weights among them, and
-// its LDS reads are done.  (The load wait is the builtin, so that the compiler
-// knows of it; the weights are named so that their loads stay before it.)
-__device__ __forceinline__ void pq_meet(double (&wt)[KC / 4]) {
-#pragma unroll
-    for (int s = 0; s < KC / 4; ++s) asm volatile("" : "+v"(wt[s]));
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// One stage's rows straight into LDS and its weights into registers.  A row past
-// k1 and a column past the operand's end read as zero (the buffers' range
-// checks), so the loop has no tail and no vector address arithmetic.
+// One T x T tile of sum_t conj(P[t][G]) w_t Q[t][H] over t in [k0, k1): raw sums
+// (no prefactor) to o, rows of ldo (tile rows >= P.n or columns >= Q.n are dropped).
 template <int T, bool W>
-__device__ __forceinline__ void pq_issue(unsigned char *__restrict__ stage, double (&wt)[KC / 4], const PqSrc &S,
-                                         long long kk, long long k1, int wave, int lane) {
-    unsigned char *dst = stage + ((wave >> 1) * KC + 4 * (wave & 1)) * T * 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const long long t = kk + 4 * (wave & 1) + i;
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(S.base + t * S.ld), 0, t < k1 ? S.bytes : 0, 0x00020000);
-        if (T == 64 || lane < T)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t *)(dst + i * T * 16), 16, 16 * lane, 0, 0, 0);
-    }
-    if (W) {
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(S.w + kk), 0, (int)max(0ll, min((long long)KC, k1 - kk)) * 8, 0x00020000);
-#pragma unroll
-        for (int s = 0; s < KC / 4; ++s) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, 8 * (lane >> 4) + 32 * s, 0, 0);
-            __builtin_memcpy(&wt[s], &v, 8);
-        }
-    }
-}
-
-// The MFMAs of one stage `cur` while the next one comes into `nxt` (distinct
-// restrict-qualified buffers: the loads in flight do not alias the reads).
-// Four pairs at a time: lane (li, lk) reads the complex values of pair lk, one
-// 16-byte read per operand block, and its real and imaginary parts feed two
-// MFMAs each; the only vector arithmetic is w a and a sign, per block of P.
-template <int T, bool W>
-__device__ __forceinline__ void pq_step(const unsigned char *__restrict__ cur, unsigned char *__restrict__ nxt,
-                                        double (&wt)[KC / 4], const PqSrc &S, long long kk, long long k1, int wave,
-                                        int lane, double4_t (&cre)[T / 32][T / 32], double4_t (&cim)[T / 32][T / 32]) {
-    constexpr int NB = T / 32, WT = T / 2;
-    const int wr = wave >> 1, wc = wave & 1, li = lane & 15, lk = lane >> 4;
-    double wn[KC / 4] = {};
-    if (kk + KC < k1) pq_issue<T, W>(nxt, wn, S, kk + KC, k1, wave, lane);
-    __builtin_amdgcn_sched_barrier(0);
-    const unsigned char *A = cur + (lk * T + wr * WT + li) * 16, *B = cur + (KC * T + lk * T + wc * WT + li) * 16;
-#pragma unroll
-    for (int s = 0; s < KC / 4; ++s) {
-        double2 a[NB], b[NB];
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            a[i] = *reinterpret_cast<const double2 *>(A + (4 * s * T + 16 * i) * 16);
-            b[i] = *reinterpret_cast<const double2 *>(B + (4 * s * T + 16 * i) * 16);
-        }
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            if (W) a[i] = make_double2(wt[s] * a[i].x, wt[s] * a[i].y);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                cre[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, cre[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, cim[i][j], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const double na = -a[i].y;
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                cre[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].y, cre[i][j], 0, 0, 0);
-                cim[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(na, b[j].x, cim[i][j], 0, 0, 0);
-            }
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);  // the loads have all the MFMAs' time to land
-    pq_meet(wn);
-#pragma unroll
-    for (int s = 0; s < KC / 4; ++s) wt[s] = wn[s];
-}
-
-// What bounds the tiles: the FP64 MFMAs, 16 of 64 cycles per wave and four pairs
-// (T = 64), and with them every vector instruction: the two do not overlap on
-// FP64, so the loop holds only what the sums need.  Loads go straight to LDS with
-// scalar addresses, and operands stay interleaved complex, read 16 bytes at a
-// time.  One static sum over 102400 pairs at 1500 vectors: 17.46 -> 15.27 ms per
-// call, against 14.5 ms with the LDS reads and MFMAs alone
-// and 12.2 ms at the rate of a large library FP64 product; the
-// self-energy of 404 x 64 bands at 1500 vectors, 9.45 -> 8.48 ms.  8 pairs a stage: 16
-// take 64 KB of LDS, fewer blocks fit a CU, and it was 16.7 ms.
-//
-// One T x T tile of sum_t conj(P[t][G]) w_t Q[t][H] over t in [k0, k1) (w_t
-// = 1 without weights): 4 waves in a 2 x 2 layout, each owning a (T/2) x
-// (T/2) block of 16 x 16 MFMA tiles.  P has rows of ldp values of which the
-// first m are used, Q rows of ldq with n used.  Raw sums (no prefactor) are
-// stored to o, rows of ldo (tile rows >= m or columns >= n are dropped).
-template <int T, bool W>
-__device__ __forceinline__ void pq_tile(const double2 *__restrict__ P, long long ldp, int m,
-                                        const double2 *__restrict__ Q, long long ldq, int n,
-                                        const double *__restrict__ w, int G0, int H0, long long k0, long long k1,
-                                        double2 *__restrict__ o, long long ldo, PqLds<T> &lds) {
-    constexpr int NB = T / 32;    // MFMA tiles per wave side
-    constexpr int WT = T / 2;     // wave block edge
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
-    const int li = lane & 15, lk = lane >> 4;
-
-    double4_t cre[NB][NB], cim[NB][NB];
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            cre[a][b] = (double4_t){0.0, 0.0, 0.0, 0.0};
-            cim[a][b] = (double4_t){0.0, 0.0, 0.0, 0.0};
-        }
-    PqSrc S;
-    S.base = wave < 2 ? P + G0 : Q + H0;
-    S.ld = wave < 2 ? ldp : ldq;
-    S.bytes = min(T, wave < 2 ? m - G0 : n - H0) * 16;
-    S.w = w;
-    double wt[KC / 4] = {};
-    pq_issue<T, W>(&lds.b[0][0][0], wt, S, k0, k1, wave, lane);
-    pq_meet(wt);
-    unsigned char *cur = &lds.b[0][0][0], *nxt = &lds.b[1][0][0];
-#pragma unroll 1
-    for (long long kk = k0; kk < k1; kk += KC) {
-        pq_step<T, W>(cur, nxt, wt, S, kk, k1, wave, lane, cre, cim);
-        unsigned char *t = cur;
-        cur = nxt;
-        nxt = t;
-    }
-    // D layout of v_mfma_f64_16x16x4: lane l, register r -> row 4r + l/16, col l%16
+__device__ __forceinline__ void pq_tile(const PqOp &P, const PqOp &Q, const double *__restrict__ w, int G0, int H0,
+                                        long long k0, long long k1, double2 *__restrict__ o, long long ldo,
+                                        PqLds<T> &lds) {
+    double4_t cre[T / 32][T / 32], cim[T / 32][T / 32];
+    pq_sums<T, W, false>(P, Q, w, G0, H0, k0, k1, cre, cim, lds, [] {});
     global_double2 *og = as_global(o);
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int G = G0 + wr * WT + 16 * a + 4 * r + lk;
-                const int H = H0 + wc * WT + 16 * b + li;
-                if (G < m && H < n) {
-                    global_double2 &e = og[(size_t)G * ldo + H];
-                    e.x = cre[a][b][r];
-                    e.y = cim[a][b][r];
-                }
-            }
+    pq_each<T>([&](int a, int b, int r, int g, int h) {
+        if (G0 + g < P.n && H0 + h < Q.n) {
+            global_double2 &e = og[(size_t)(G0 + g) * ldo + H0 + h];
+            e.x = cre[a][b][r];
+            e.y = cim[a][b][r];
+        }
+    });
 }
 
 // The chi-sum tile: P = Q = M, rows of ng, weights w.
@@ -230,7 +76,8 @@ template <int T>
 __device__ __forceinline__ void herk_tile(const double2 *__restrict__ M, int ng, const double *__restrict__ w,
                                           int G0, int H0, long long k0, long long k1, double2 *__restrict__ o,
                                           PqLds<T> &lds) {
-    pq_tile<T, true>(M, ng, ng, M, ng, ng, w, G0, H0, k0, k1, o, ng, lds);
+    const PqOp op = {M, ng, ng};
+    pq_tile<T, true>(op, op, w, G0, H0, k0, k1, o, ng, lds);
 }
 }  // namespace
 
@@ -332,7 +179,7 @@ __global__ __launch_bounds__(256, 3) void k_gemm_phq(const GemmProb G) {
         const long long split = item / ntile, tile = item % ntile;
         const int tr = (int)(tile / G.ntc), tc = (int)(tile % G.ntc);
         const long long k0 = split * G.kper, k1 = min(G.K, k0 + G.kper);
-        pq_tile<T, false>(G.P, G.ldp, G.m, G.Q, G.ldq, G.n, nullptr, tr * T, tc * T, k0, k1,
+        pq_tile<T, false>({G.P, G.ldp, G.m}, {G.Q, G.ldq, G.n}, nullptr, tr * T, tc * T, k0, k1,
                           G.out + (size_t)split * G.m * G.n, G.n, lds);
     }
 }

@@ -35,10 +35,9 @@
 #include <utility>
 
 #include "common.h"
+#include "f64_tile.h"
 
 namespace bgw {
-
-typedef double double4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kPanelMax = 32;
 constexpr int kGjeMaxR = 48;                // workgroups per matrix (n <= 12288, 256 rows each; the narrow
@@ -472,137 +471,33 @@ __global__ __launch_bounds__(64) void k_gje_swap_save(double2 *__restrict__ A, i
     }
 }
 
-namespace {
-constexpr int UT = 64;            // update tile (rows and cols)
-constexpr int ULD = UT + 4;       // padded LDS row
-}  // namespace
-
-// A[:, cs] += P * R with P = A[:, r0:r0+nbr] (n x nbr) and R = Rs (nbr x m),
-// complex, as two real products over the interleaved index kk = 2j + part:
-//   Re += sum_kk P'[i][kk] Bre[kk][c],  Bre[2j] = Re R, Bre[2j+1] = -Im R
-//   Im += sum_kk P'[i][kk] Bim[kk][c],  Bim[2j] = Im R, Bim[2j+1] =  Re R
-// The panel is staged kPanelMax columns at a time, the next chunk loaded
-// into registers while the current one feeds the MFMAs.
+// A[:, cs] += P * R with P = A[:, r0:r0+nbr] (n x nbr) and R = Rs (nbr x m); the
+// old values of the tile are fetched under the last stage's MFMAs.  Bound by the
+// FP64 MFMAs at 128 columns per update (16 flops per byte of A moved) and by
+// latency in the narrow updates within an outer block.  Four matrices of 4000
+// without interchanges, whole inversions: 48.0 -> 41.3 ms against a tile loop that
+// staged both operands through registers.
+template <int T>
 __global__ __launch_bounds__(256, 2) void k_gje_update(double2 *__restrict__ A, int n, int r0, int nbr, GjeCols cs,
                                                     const double2 *__restrict__ Rs) {
-    __shared__ double Ps[2 * kPanelMax][ULD];
-    __shared__ double Rsh[2 * kPanelMax][ULD];
-    const int mat = blockIdx.z;
-    double2 *Am = A + (size_t)mat * n * n;
-    const int m = cs.count();
-    const double2 *R = Rs + (size_t)mat * nbr * m;
-    const int I0 = blockIdx.x * UT, C0 = blockIdx.y * UT;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1, li = lane & 15, lk = lane >> 4;
-
-    double4_t cre[2][2], cim[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            cre[a][b] = (double4_t){0.0, 0.0, 0.0, 0.0};
-            cim[a][b] = (double4_t){0.0, 0.0, 0.0, 0.0};
-        }
-    // P and R tiles of one chunk of kPanelMax panel columns, loaded into
-    // registers one chunk ahead: the loads of chunk j0 + kPanelMax are issued
-    // before the MFMAs of chunk j0
-    constexpr int SIT = UT * kPanelMax / 256;
-    double2 pv[SIT], rw[SIT];
-    auto load_chunk = [&](int j0) {
-        const int nbc = min(kPanelMax, nbr - j0);
-#pragma unroll
-        for (int it = 0; it < SIT; ++it) {
-            const int e = tid + 256 * it;
-            const int i = e / kPanelMax, j = e % kPanelMax;  // P tile: row i, panel col j
-            pv[it] = (I0 + i < n && j < nbc) ? Am[(size_t)(I0 + i) * n + r0 + j0 + j] : make_double2(0.0, 0.0);
-            const int jr = e / UT, c = e % UT;  // R tile: panel row jr, col c
-            rw[it] = (jr < nbc && C0 + c < m) ? R[(size_t)(j0 + jr) * m + C0 + c] : make_double2(0.0, 0.0);
-        }
-    };
-    // this lane's elements of the output tile, fetched during the last chunk
-    double2 old[2][2][4];
-    auto load_old = [&]() {
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = I0 + wr * 32 + 16 * a + 4 * r + lk;
-                    const int cp = C0 + wc * 32 + 16 * b + li;
-                    old[a][b][r] = make_double2(0.0, 0.0);
-                    if (i < n && cp < m) old[a][b][r] = Am[(size_t)i * n + cs.col(cp)];
-                }
-    };
-    const double rsign = (lk & 1) ? -1.0 : 1.0;  // kr = 4 s + lk has the parity of lk
-    auto stage_chunk = [&]() {
-#pragma unroll
-        for (int it = 0; it < SIT; ++it) {
-            const int e = tid + 256 * it;
-            const int i = e / kPanelMax, j = e % kPanelMax;
-            Ps[2 * j][i] = pv[it].x;
-            Ps[2 * j + 1][i] = pv[it].y;
-            const int jr = e / UT, c = e % UT;
-            Rsh[2 * jr][c] = rw[it].x;
-            Rsh[2 * jr + 1][c] = rw[it].y;
-        }
-    };
-    auto mfma_step = [&](int s) {
-        const int kr = 4 * s + lk;
-        double av[2], bre[2], bim[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) av[a] = Ps[kr][wr * 32 + 16 * a + li];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int col = wc * 32 + 16 * b + li;
-            // odd rows (imaginary parts): Bre = -Im R, Bim = Re R; even: Re R, Im R
-            bre[b] = rsign * Rsh[kr][col];
-            bim[b] = Rsh[kr ^ 1][col];
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                cre[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bre[b], cre[a][b], 0, 0, 0);
-                cim[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bim[b], cim[a][b], 0, 0, 0);
-            }
-    };
-    // a full chunk has a compile-time step count; the last one may be narrower
-    auto mfma_chunk = [&](int nbc) {
-        if (nbc == kPanelMax) {
-#pragma unroll 4
-            for (int s = 0; s < 2 * kPanelMax / 4; ++s) mfma_step(s);
-        } else {
-            const int ksteps = (2 * nbc + 3) / 4;
-            for (int s = 0; s < ksteps; ++s) mfma_step(s);
-        }
-    };
-    load_chunk(0);
-    int j0 = 0;
-    for (; j0 + kPanelMax < nbr; j0 += kPanelMax) {
-        stage_chunk();
-        __syncthreads();
-        load_chunk(j0 + kPanelMax);
-        mfma_chunk(kPanelMax);
-        __syncthreads();  // this chunk's LDS reads are done
-    }
-    // the last chunk: the output tile's old values are fetched under its MFMAs
-    stage_chunk();
-    __syncthreads();
-    load_old();
-    mfma_chunk(nbr - j0);
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = I0 + wr * 32 + 16 * a + 4 * r + lk;
-                const int cp = C0 + wc * 32 + 16 * b + li;
-                if (i < n && cp < m)
-                    Am[(size_t)i * n + cs.col(cp)] =
-                        make_double2(old[a][b][r].x + cre[a][b][r], old[a][b][r].y + cim[a][b][r]);
-            }
+    __shared__ PqLds<T> lds;
+    double2 *Am = A + (size_t)blockIdx.z * n * n;
+    const int m = cs.count(), I0 = blockIdx.x * T, C0 = blockIdx.y * T;
+    double4_t cre[T / 32][T / 32], cim[T / 32][T / 32];
+    double2 old[T / 32][T / 32][4];
+    pq_sums<T, false, true>({Am + r0, n, n}, {Rs + (size_t)blockIdx.z * nbr * m, m, m}, nullptr, I0, C0, 0, nbr, cre,
+                            cim, lds, [&] {
+                                pq_each<T>([&](int a, int b, int r, int i, int c) {
+                                    old[a][b][r] = make_double2(0.0, 0.0);
+                                    if (I0 + i < n && C0 + c < m)
+                                        old[a][b][r] = Am[(size_t)(I0 + i) * n + cs.col(C0 + c)];
+                                });
+                            });
+    pq_each<T>([&](int a, int b, int r, int i, int c) {
+        if (I0 + i < n && C0 + c < m)
+            Am[(size_t)(I0 + i) * n + cs.col(C0 + c)] =
+                make_double2(old[a][b][r].x + cre[a][b][r], old[a][b][r].y + cim[a][b][r]);
+    });
 }
 
 // Column index map of the final column interchanges: start from the identity
@@ -965,6 +860,25 @@ static char *align256(char *p) { return (char *)(((uintptr_t)p + 255) & ~(uintpt
 // matrix takes one rank-(outer width) update per outer block.
 static int gje_outer_nb(int n) { return n >= 3000 ? 4 * kPanelMax : 2 * kPanelMax; }
 
+template <int T>
+static void launch_gje_update_t(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, const double2 *Rs,
+                                hipStream_t st) {
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_gje_update<T>), dim3((n + T - 1) / T, (cs.count() + T - 1) / T, nmat),
+                       dim3(256), 0, st, A, n, r0, nbr, cs, Rs);
+}
+
+// 64-wide tiles read half as much per product; below 2000 of them (eight per
+// CU) the last ones leave most of the chip idle, and 32-wide tiles finish first:
+// one matrix of 1500, 64 columns per update (576 tiles), 2.49 ms in 64-wide tiles
+// for the whole inversion, 2.35 in 32-wide ones; four of 4000 (15876 tiles) 41.3
+// and 43.8 ms.
+static void launch_gje_update(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, const double2 *Rs,
+                              hipStream_t st) {
+    const long long t64 = (long long)((n + 63) / 64) * ((cs.count() + 63) / 64) * nmat;
+    if (t64 < 2000) launch_gje_update_t<32>(A, n, nmat, r0, nbr, cs, Rs, st);
+    else launch_gje_update_t<64>(A, n, nmat, r0, nbr, cs, Rs, st);
+}
+
 // Row interchanges and rank-nbr update of the panel [r0, r0 + nbr) applied to
 // the columns cs: A[:, cs] = swapped, panel rows saved and zeroed, += P Rs.
 static int gje_apply(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, const int *ipiv, double2 *Rs,
@@ -972,8 +886,7 @@ static int gje_apply(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, c
     const int m = cs.count();
     if (m <= 0) return BGW_OK;
     hipLaunchKernelGGL(k_gje_swap_save, dim3((m + 63) / 64, nmat), dim3(64), 0, st, A, n, r0, nbr, cs, ipiv, Rs);
-    hipLaunchKernelGGL(k_gje_update, dim3((n + UT - 1) / UT, (m + UT - 1) / UT, nmat), dim3(256), 0, st, A, n, r0,
-                       nbr, cs, (const double2 *)Rs);
+    launch_gje_update(A, n, nmat, r0, nbr, cs, Rs, st);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
@@ -1407,8 +1320,7 @@ static int nsd_apply(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, d
     const int m = cs.count();
     if (m <= 0) return BGW_OK;
     hipLaunchKernelGGL(k_nsd_save, dim3((m + 255) / 256, nbr, nmat), dim3(256), 0, st, A, n, r0, nbr, cs, Rs);
-    hipLaunchKernelGGL(k_gje_update, dim3((n + UT - 1) / UT, (m + UT - 1) / UT, nmat), dim3(256), 0, st, A, n, r0,
-                       nbr, cs, (const double2 *)Rs);
+    launch_gje_update(A, n, nmat, r0, nbr, cs, Rs, st);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
