@@ -50,7 +50,8 @@ int gje_max_group(int n);
 int launch_gje_invert(double2 *A, int n, int nmat, int *info, void *ws, int *ipiv_ws, hipStream_t);
 size_t nsd_workspace_bytes(int n, int nmat, int nall);
 int launch_nsd_check(const double2 *chi, const double *v, int n, int nall, int nmat, void *ws, hipStream_t);
-int launch_nsd_invert(double2 *A, int n, int nmat, int m0, int nall, int *info, void *ws, hipStream_t);
+int launch_nsd_build(const double2 *chi, const double *v, int n, int nall, int nmat, double2 *out, void *ws, hipStream_t);
+int launch_nsd_invert(double2 *A, const double *v, int n, int nmat, int m0, int nall, int *info, void *ws, hipStream_t);
 
 namespace {
 thread_local std::string g_err;
@@ -727,12 +728,12 @@ extern "C" int bgw_eps_inv_nsd(bgw_handle_t h, int ng, int nw, const double *vco
         Timed tm(h, BGW_KERNEL_EPS_BUILD, st);
         // chi is read before epsilon overwrites it (the call may be in place)
         BGW_TRY(launch_nsd_check((const double2 *)chi, vcoul, ng, nw, group, h->ws.p, st));
-        BGW_TRY(launch_eps_build((const double2 *)chi, vcoul, ng, nw, (double2 *)epsinv, st));
+        BGW_TRY(launch_nsd_build((const double2 *)chi, vcoul, ng, nw, group, (double2 *)epsinv, h->ws.p, st));
     }
     Timed tm(h, BGW_KERNEL_INVERT, st);
     for (int w0 = 0; w0 < nw; w0 += group) {
         const int gn = std::min(group, nw - w0);
-        BGW_TRY(launch_nsd_invert((double2 *)epsinv + (size_t)w0 * ng * ng, ng, gn, w0, nw, info + w0, h->ws.p, st));
+        BGW_TRY(launch_nsd_invert((double2 *)epsinv + (size_t)w0 * ng * ng, vcoul, ng, gn, w0, nw, info + w0, h->ws.p, st));
     }
     return BGW_OK;
 }

@@ -1055,23 +1055,36 @@ int gje_max_group(int n) {
 //                and of sqrt(v_G v_G') |chi_GG'| (read before epsilon is
 //                built in place), +inf when some v <= 0 or a value is not
 //                finite;
-//   k_nsd_diag   one workgroup per matrix inverts the panel's diagonal block
-//                D (kNsdNb x kNsdNb, registers, one barrier per step) in
-//                place and into Dinv, watching every pivot;
-//   k_nsd_rows   the panel's other rows become -A[i, K] D^-1, all rows in
-//                parallel;
-//   k_nsd_save   the panel rows of the other columns copied and zeroed, one
-//                workgroup row per panel row;
-// then the pivoted path's rank update (k_gje_update), in the same two-level
-// outer blocks.  A
-// matrix whose chi is not Hermitian to 1e-8 (relative, on the symmetrised
+//   k_nsd_build  epsilon, or epst;
+//   k_nsd_diag   one workgroup per matrix inverts the panel's 64 x 64 diagonal
+//                block, watching every pivot;
+//   k_nsd_rows   the rest of the panel, one 64-term MFMA product per element;
+//   k_nsd_update the rank update of the other columns, by outer blocks of one
+//                panel (n < 3000) or two: the matrix then streams through memory
+//                once per 128 columns, which at n = 4000 is what the MFMAs need.
+// epst is Hermitian exactly where chi is, and elimination keeps it so up to a sign
+// (rows eliminated against rows that are not: the conjugate transpose changes
+// sign).  Such a matrix is therefore eliminated as epst, on and above the diagonal
+// only: half the products.  W = Dinv R of the panel's rows R is also, conjugate
+// transposed, the panel's columns, so that both operands of the update lie in rows.
+// k_nsd_unscale makes the whole eps^-1 of it.  A matrix that is Hermitian only to
+// 1e-8, not to 2^-50 of its largest element (a few roundings; the lower triangle
+// then holds information of its own), is eliminated in general form, as eps, by
+// the same launches; which of the two is decided on the device, from k_nsd_check.
+// A matrix whose chi is not Hermitian to 1e-8 (relative, on the symmetrised
 // scale) or has v <= 0 gets info = -2; one with a pivot whose real part is
 // below 1/2, or that is not real to half of it, gets info = -3 (chi not
 // negative semidefinite).  Either way epsinv is unspecified.
+//
+// Bounds and figures.  n = 1500: 2.35 -> 1.29 ms, three launches a panel, of which
+// the diagonal block (a serial chain) takes 23 of 53 us, the update 20, the rows 8.
+// Four matrices of 4000: 41.3 -> 22.6 ms, 17.2 of them in the update at 61 TFLOP/s
+// of FP64 MFMA.  k_nsd_diag: 51 -> 23 us; its 64 pivots take 7.5 us of that (one
+// wave, no LDS round trip or barrier per pivot), the MFMA steps 5, loads, stores
+// and the launch the rest.  k_nsd_rows: 12.3 -> 8 us at n = 1500.
 constexpr int kNsdNb = 64;        // panel width (diagonal block size)
-constexpr int kNsdDiagThreads = 512;
-constexpr int kNsdRowsPer = 16;   // rows of one k_nsd_rows workgroup
-constexpr int kNsdTile = 32;      // tile of the Hermitian check
+constexpr int kNsdDiagThreads = 768;
+constexpr int kNsdTile = 32;      // tile of the Hermitian check and of the unscaling
 constexpr double kNsdHermTol = 1e-8;
 
 __device__ __forceinline__ void atomic_max_nonneg(double *p, double x) {
@@ -1139,78 +1152,226 @@ __global__ __launch_bounds__(256) void k_nsd_check(const double2 *__restrict__ c
     }
 }
 
-// Gauss-Jordan without interchanges on D = A[K, K], K = [ks, ks + nb),
-// padded to kNsdNb with the identity.  Thread t holds column t / 8 of the
-// rows 8 (t % 8) + r, so the eight threads of the pivot column sit in one
-// wavefront and, with the steps unrolled by eight, the pivot row's register
-// is known at compile time.  A step is one complex FMA per entry,
-// d -= f_i s_j with f the old pivot column and s the new pivot row
-// (inv * old row); the pivot row and column are then set exactly: row c to
-// s, column c to -f inv, (c, c) to inv.  The pivot row and column go
-// through LDS, double-buffered (one barrier per step), and every LDS read of
-// a step is issued before its arithmetic.
+// The form a matrix takes (see above): Hermitian to 2^-50 of its scale, or general.
+__device__ __forceinline__ bool nsd_hermitian(const double *chk, int mat) {
+    const double nh = chk[2 * mat], mx = chk[2 * mat + 1];
+    return mx <= DBL_MAX && nh <= 0x1p-50 * mx;
+}
+
+// epst (every 64-block on or above the diagonal) or eps.  One row per workgroup, grid
+// (n, matrices); chi and out may be the same.
+__global__ __launch_bounds__(256) void k_nsd_build(const double2 *chi, const double *__restrict__ v, int n,
+                                                   const double *__restrict__ chk, double2 *out) {
+    const int i = blockIdx.x;
+    const size_t row = ((size_t)blockIdx.y * n + i) * n;
+    const double vi = v[i], si = sqrt(vi);
+    const bool herm = nsd_hermitian(chk, blockIdx.y);
+    for (int j = (herm ? i & ~(kNsdNb - 1) : 0) + threadIdx.x; j < n; j += 256) {
+        const double2 x = chi[row + j];
+        const double f = herm ? si * sqrt(v[j]) : vi;
+        out[row + j] = make_double2((i == j ? 1.0 : 0.0) - f * x.x, -f * x.y);
+    }
+}
+
+// eps^-1 = S X S^-1 of a Hermitian matrix from the upper triangle of X = epst^-1, in
+// place; tile pairs (I <= J) row by row, grid (pairs, matrices).
+__global__ __launch_bounds__(256) void k_nsd_unscale(double2 *__restrict__ A, const double *__restrict__ v, int n,
+                                                     int tiles, const double *__restrict__ chk) {
+    __shared__ double2 X[kNsdTile][kNsdTile + 1];
+    __shared__ double sv[2][kNsdTile], rv[2][kNsdTile];
+    if (!nsd_hermitian(chk, blockIdx.y)) return;
+    int I = 0, rem = blockIdx.x;
+    while (rem >= tiles - I) {
+        rem -= tiles - I;
+        ++I;
+    }
+    const int J = I + rem, tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+    const int I0 = I * kNsdTile, J0 = J * kNsdTile;
+    double2 *Am = A + (size_t)blockIdx.y * n * n;
+    if (tid < 2 * kNsdTile) {
+        const int g = (tid < kNsdTile ? I0 : J0) + tx;
+        const double s = g < n ? sqrt(v[g]) : 1.0;
+        sv[tid >> 5][tx] = s;
+        rv[tid >> 5][tx] = 1.0 / s;
+    }
+#pragma unroll
+    for (int r = 0; r < kNsdTile; r += 8) {
+        const int i = I0 + ty + r, j = J0 + tx;
+        X[ty + r][tx] = (i < n && j < n) ? Am[(size_t)i * n + j] : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kNsdTile; r += 8) {
+        const int i = I0 + ty + r, j = J0 + tx;
+        if (i <= j && j < n) {
+            const double f = sv[0][ty + r] * rv[1][tx];
+            Am[(size_t)i * n + j] = make_double2(f * X[ty + r][tx].x, f * X[ty + r][tx].y);
+        }
+        const int h = J0 + ty + r, g = I0 + tx;  // the mirrored element (h, g)
+        if (g < h && h < n) {
+            const double f = sv[1][ty + r] * rv[0][tx];
+            Am[(size_t)h * n + g] = make_double2(f * X[tx][ty + r].x, -f * X[tx][ty + r].y);
+        }
+    }
+}
+
+// c += a b, complex, four terms of the contraction
+__device__ __forceinline__ void cmfma(double4_t &re, double4_t &im, double2 a, double2 b) {
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im, 0, 0, 0);
+}
+
+// x of lane C of every group of 16 lanes, and of lane 16 G + (own lane mod 16)
+template <int C>
+__device__ __forceinline__ double row_lane(double x) {
+    return __longlong_as_double(__builtin_amdgcn_mov_dpp(__double_as_longlong(x), 0x150 + C, 0xf, 0xf, true));
+}
+template <int G>
+__device__ __forceinline__ double group_lane(double x, int lane) {
+    const long long b = __double_as_longlong(x);
+    const int at = (16 * G + (lane & 15)) * 4;
+    const int lo = __builtin_amdgcn_ds_bpermute(at, (int)b), hi = __builtin_amdgcn_ds_bpermute(at, (int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <int L>
+__device__ __forceinline__ double one_lane(double x) {
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)b, L), hi = __builtin_amdgcn_readlane((int)(b >> 32), L);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Gauss-Jordan step C of a 16 x 16 block held by one wave, lane (r, g) = (lane mod 16,
+// lane / 16) with columns 4 g .. 4 g + 3 of row r: with inv = 1 / pivot and the
+// multipliers q_r = (old column C) inv, except q_C = -inv, every other column's
+// entry becomes (r == C ? 0 : old) - q_r (old row C) and column C becomes -q_r.
+template <int C>
+__device__ __forceinline__ void inv16_step(double2 (&d)[4], int lane, bool &bad) {
+    constexpr int Q = C % 4, G = C / 4;
+    const bool prow = (lane & 15) == C, pcol = (lane >> 4) == G;
+    const double2 p = make_double2(one_lane<16 * G + C>(d[Q].x), one_lane<16 * G + C>(d[Q].y));
+    const double2 f = make_double2(group_lane<G>(d[Q].x, lane), group_lane<G>(d[Q].y, lane));
+    bad |= !(p.x >= 0.5 && fabs(p.y) <= 0.5 * p.x);
+    // 1 / |p|^2 (p >= 1/2, or the result is of no use) to an ulp: two Newton steps
+    const double den = fma(p.x, p.x, p.y * p.y);
+    double rden = __builtin_amdgcn_rcp(den);
+    rden = fma(fma(-den, rden, 1.0), rden, rden);
+    rden = fma(fma(-den, rden, 1.0), rden, rden);
+    const double2 inv = make_double2(p.x * rden, -p.y * rden);
+    double2 q = cmul(f, inv);
+    if (prow) q = make_double2(-inv.x, -inv.y);
+    const double keep = prow ? 0.0 : 1.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int c = (C + 1 + i) % 4;  // the next pivot's column first
+        const double2 row = make_double2(row_lane<C>(d[c].x), row_lane<C>(d[c].y));
+        d[c] = cfms(make_double2(keep * d[c].x, keep * d[c].y), q, row);
+    }
+    if (pcol) d[Q] = make_double2(-q.x, -q.y);
+}
+template <int... C>
+__device__ __forceinline__ void inv16(double2 (&d)[4], int lane, bool &bad, std::integer_sequence<int, C...>) {
+    (inv16_step<C>(d, lane, bad), ...);
+}
+
+// D = A[K, K], K = [ks, ks + nb), padded to 64 with the identity, inverted in place and
+// into Dinv (the whole 64 x 64), no interchanges, by blocks of 16: with Dk the
+// inverse of diagonal block k,
+//   row block k:     W = Dk D[k, :]       (k_th columns: Dk)
+//   other blocks:    D[a, b] -= D[a, k] W[b],  D[a, k] = -D[a, k] Dk.
+// One workgroup per matrix, D in LDS; 12 waves, one 16 x 16 MFMA product each per
+// block step, wave 0 with the next diagonal block, which it then inverts in its
+// registers while the others finish.
 __global__ __launch_bounds__(kNsdDiagThreads) void k_nsd_diag(double2 *__restrict__ A, int n, int ks, int nb,
                                                               double2 *__restrict__ Dinv,
                                                               const double *__restrict__ chk, int *__restrict__ info) {
-    constexpr int CPT = kNsdDiagThreads / kNsdNb;  // threads per column
-    constexpr int RPT = kNsdNb / CPT;              // rows per thread
-    __shared__ double2 rowb[2][kNsdNb], colb[2][kNsdNb];
+    constexpr int LD = 17;                          // padded rows of 16
+    __shared__ double2 D[kNsdNb * kNsdNb];
+    __shared__ double2 Cb[kNsdNb * LD];             // column block k before the step
+    __shared__ double2 Dk[16 * LD];                 // inverse of diagonal block k
     const int mat = blockIdx.x;
     double2 *Am = A + (size_t)mat * n * n;
-    const int t = threadIdx.x, j = t / CPT, rg = t % CPT;  // rows RPT rg + r
-    double2 d[RPT];
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int i = RPT * rg + r;
-        d[r] = (i < nb && j < nb) ? Am[(size_t)(ks + i) * n + ks + j] : make_double2(i == j ? 1.0 : 0.0, 0.0);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    for (int e = tid; e < kNsdNb * kNsdNb; e += kNsdDiagThreads) {
+        const int i = e / kNsdNb, j = e % kNsdNb;
+        D[e] = (i < nb && j < nb) ? Am[(size_t)(ks + i) * n + ks + j] : make_double2(i == j ? 1.0 : 0.0, 0.0);
     }
+    __syncthreads();
     bool bad = false;
-    for (int cb = 0; cb * RPT < nb; ++cb) {
-        const bool holder = rg == cb;  // this thread holds the pivot rows of these RPT steps
+    const int nk = (nb + 15) / 16;
+    // step -1 only inverts block 0 (the inversion's code, which every launch fetches
+    // anew, stands once)
+#pragma unroll 1
+    for (int k = -1; k < nk; ++k) {
+        if (k >= 0) {
+            if (wave < 3) {  // W, in place of row block k
+                const int b = (k + 1 + wave) & 3;
+                double2 x[4];
 #pragma unroll
-        for (int cr = 0; cr < RPT; ++cr) {
-            const int c = cb * RPT + cr;
-            if (c >= nb) break;
-            const int b = c & 1;
-            if (holder) rowb[b][j] = d[cr];
-            if (j == c) {
+                for (int t = 0; t < 4; ++t) x[t] = D[(16 * k + 4 * t + lk) * kNsdNb + 16 * b + li];
+                double4_t re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int r = 0; r < RPT; ++r) colb[b][RPT * rg + r] = d[r];
+                for (int t = 0; t < 4; ++t) cmfma(re, im, Dk[li * LD + 4 * t + lk], x[t]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    D[(16 * k + 4 * r + lk) * kNsdNb + 16 * b + li] = make_double2(re[r], im[r]);
+            } else if (wave < 6) {  // column block k, kept for the updates
+                const int a = (k + wave - 2) & 3;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = 16 * a + 4 * r + lk;
+                    Cb[i * LD + li] = D[i * kNsdNb + 16 * k + li];
+                }
+            } else if (wave == 6) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    D[(16 * k + 4 * r + lk) * kNsdNb + 16 * k + li] = Dk[(4 * r + lk) * LD + li];
             }
             __syncthreads();
-            const double2 p = rowb[b][c];
-            const double2 rj = rowb[b][j];
-            double2 f[RPT];
+        }
+        // block (a, b): -D[a, k] Dk at b = k, else D[a, b] - D[a, k] W[b]
+        const int a = (k + 1 + wave / 4) & 3, b = (k + 1 + wave % 4) & 3;
+        double4_t re, im;
 #pragma unroll
-            for (int r = 0; r < RPT; ++r) f[r] = colb[b][RPT * rg + r];
-            __builtin_amdgcn_sched_barrier(0);
-            bad |= !(p.x >= 0.5 && fabs(p.y) <= 0.5 * p.x);
-            const double rden = 1.0 / (p.x * p.x + p.y * p.y);
-            const double2 inv = make_double2(p.x * rden, -p.y * rden);
-            const double2 sj = cmul(inv, rj);
+        for (int r = 0; r < 4; ++r) {
+            const double2 x = D[(16 * a + 4 * r + lk) * kNsdNb + 16 * b + li];
+            re[r] = b == k ? 0.0 : x.x;
+            im[r] = b == k ? 0.0 : x.y;
+        }
+        if (k >= 0) {
 #pragma unroll
-            for (int r = 0; r < RPT; ++r) d[r] = cfms(d[r], f[r], sj);
-            if (holder) d[cr] = sj;
-            if (j == c) {
-#pragma unroll
-                for (int r = 0; r < RPT; ++r) {
-                    const double2 fi = cmul(f[r], inv);
-                    d[r] = make_double2(-fi.x, -fi.y);
-                }
-                if (holder) d[cr] = inv;
+            for (int t = 0; t < 4; ++t) {
+                const double2 x = Cb[(16 * a + li) * LD + 4 * t + lk];
+                cmfma(re, im, make_double2(-x.x, -x.y), D[(16 * k + 4 * t + lk) * kNsdNb + 16 * b + li]);
             }
         }
+        if (wave == 0 && k + 1 < nk) {  // the next diagonal block (4 r + lk, li), inverted into Dk
+            double2 d[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Dk[(4 * r + lk) * LD + li] = make_double2(re[r], im[r]);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int c = 0; c < 4; ++c) d[c] = Dk[li * LD + 4 * lk + c];
+            inv16(d, lane, bad, std::make_integer_sequence<int, 16>{});
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Dk[li * LD + 4 * lk + c] = d[c];
+        } else if (k >= 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                D[(16 * a + 4 * r + lk) * kNsdNb + 16 * b + li] = make_double2(re[r], im[r]);
+        }
+        __syncthreads();
     }
     double2 *Dm = Dinv + (size_t)mat * kNsdNb * kNsdNb;
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int i = RPT * rg + r;
-        if (i < nb && j < nb) {
-            Am[(size_t)(ks + i) * n + ks + j] = d[r];
-            Dm[i * kNsdNb + j] = d[r];
-        }
+    for (int e = tid; e < kNsdNb * kNsdNb; e += kNsdDiagThreads) {
+        const int i = e / kNsdNb, j = e % kNsdNb;
+        const double2 x = D[e];
+        if (i < nb && j < nb) Am[(size_t)(ks + i) * n + ks + j] = x;
+        Dm[e] = x;
     }
-    if (t == 0) {
+    if (tid == 0) {
         if (ks == 0) {
             const double nh = chk[2 * mat], mx = chk[2 * mat + 1];
             if (!(mx <= DBL_MAX && nh <= kNsdHermTol * mx)) info[mat] = -2;
@@ -1219,63 +1380,225 @@ __global__ __launch_bounds__(kNsdDiagThreads) void k_nsd_diag(double2 *__restric
     }
 }
 
-// A[i, K] = -A[i, K] Dinv for the rows i outside K of one block of kNsdRowsPer
-// rows.  Thread t: row t / 16, columns t % 16 + 16 q.
-__global__ __launch_bounds__(256) void k_nsd_rows(double2 *__restrict__ A, int n, int ks, int nb,
-                                                  const double2 *__restrict__ Dinv) {
-    extern __shared__ double2 nsd_lds[];
-    constexpr int ALD = kNsdNb + 1;
-    constexpr int CG = 256 / kNsdRowsPer;  // column groups
-    constexpr int NQ = kNsdNb / CG;
-    double2 *Ds = nsd_lds;                        // [kNsdNb][kNsdNb]
-    double2 *As = nsd_lds + kNsdNb * kNsdNb;      // [kNsdRowsPer][ALD]
+// The rest of panel K = [ks, ks + nb) of outer block O = [k, ke), 16 rows and columns g
+// outside K per workgroup, one 16 x 16 MFMA tile of 64 terms per wave.
+//
+// Hermitian: W = Dinv R with R = A[K, g] (g before K: -conj(A[g, K])); R to Rs for
+// g outside O, W in place of A[K, g] and, before K, conj(W) in place of A[g, K].  An
+// outer block of two panels K1, K2 takes two passes: the first (MODE 1) leaves W1
+// = D1 R1 and R2 - D21 W1 in rows K1 and K2; the second (MODE 2), after K2's
+// diagonal block has been inverted, W2 = D2 (R2 - D21 W1) and W1 - (D1 D12) W2,
+// which together are O's inverse applied to (R1, R2).  For g in O itself R stands
+// for the identity's columns, and rows K of those columns become O's inverse; D1 D12
+// is handed from the first pass to the second in Rs's unused columns K1, transposed.
+//
+// General: A[g, K] = -A[g, K] Dinv, and A[K, g] to Rs and zeroed.
+template <int MODE>
+__global__ __launch_bounds__(256) void k_nsd_rows(double2 *__restrict__ A, int n, int k, int ke, int ks, int nb,
+                                                  const double2 *__restrict__ Dinv, double2 *__restrict__ Rs, int nbo,
+                                                  const double *__restrict__ chk) {
+    __shared__ double2 Wl[kNsdNb * 16];
     const int mat = blockIdx.y;
-    double2 *Am = A + (size_t)mat * n * n;
+    double2 *Am = A + (size_t)mat * n * n, *R = Rs + (size_t)mat * nbo * n;
     const double2 *Dm = Dinv + (size_t)mat * kNsdNb * kNsdNb;
-    const int i0 = blockIdx.x * kNsdRowsPer, tid = threadIdx.x;
-    for (int e = tid; e < kNsdNb * kNsdNb; e += 256) {
-        const int k = e / kNsdNb, jj = e % kNsdNb;
-        Ds[e] = (k < nb && jj < nb) ? Dm[e] : make_double2(0.0, 0.0);
-    }
-    for (int e = tid; e < kNsdRowsPer * kNsdNb; e += 256) {
-        const int il = e / kNsdNb, k = e % kNsdNb, i = i0 + il;
-        As[il * ALD + k] = (i < n && k < nb) ? Am[(size_t)i * n + ks + k] : make_double2(0.0, 0.0);
-    }
-    __syncthreads();
-    const int il = tid / CG, cg = tid % CG;
-    double2 acc[NQ];
+    const bool herm = nsd_hermitian(chk, mat);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    const int g0 = blockIdx.x * 16, g = g0 + li, T0 = 16 * wave;
+    const bool live = g < n, outer = g0 < k || g0 >= ke, own = g0 >= ks && g0 < ks + kNsdNb;
+    const bool low = herm && g0 < k;
+    const int K2 = k + kNsdNb, nb2 = ke - K2;  // MODE 1 and 2
+    if (own && (MODE == 0 || !herm)) return;
+    double4_t re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+    if (own) {  // the identity's columns
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] = make_double2(0.0, 0.0);
-    for (int k = 0; k < nb; ++k) {
-        const double2 a = As[il * ALD + k];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const double2 x = Ds[k * kNsdNb + cg + CG * q];
-            acc[q].x = fma(a.x, x.x, fma(-a.y, x.y, acc[q].x));
-            acc[q].y = fma(a.x, x.y, fma(a.y, x.x, acc[q].y));
+        for (int r = 0; r < 4; ++r) {
+            const double2 x = Dm[(T0 + 4 * r + lk) * kNsdNb + (g - ks)];
+            re[r] = x.x;
+            im[r] = x.y;
         }
-    }
-    const int i = i0 + il;
-    if (i < n && (i < ks || i >= ks + nb)) {
+    } else {
+        double2 a[16], b[16];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int jj = cg + CG * q;
-            if (jj < nb) Am[(size_t)i * n + ks + jj] = make_double2(-acc[q].x, -acc[q].y);
+        for (int s = 0; s < 16; ++s) {
+            const int t = 4 * s + lk;
+            a[s] = Dm[t * kNsdNb + T0 + li];
+            b[s] = make_double2(0.0, 0.0);
+            if (live && t < nb)
+                b[s] = !herm || (low && MODE != 2) ? Am[(size_t)g * n + ks + t] : Am[(size_t)(ks + t) * n + g];
+        }
+        if (herm) {
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                a[s].y = -a[s].y;  // Dinv[T][t] = conj(Dinv[t][T])
+                if (low && MODE != 2) b[s].x = -b[s].x;
+            }
+            if (MODE != 2 && outer && live) {
+#pragma unroll
+                for (int s = 0; s < 16; ++s)
+                    if (s / 4 == wave && 4 * s + lk < nb) R[(size_t)(4 * s + lk) * n + g] = b[s];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 16; ++s) cmfma(re, im, a[s], b[s]);
+    }
+    if (MODE != 0 && herm) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Wl[(T0 + 4 * r + lk) * 16 + li] = make_double2(re[r], im[r]);
+    }
+    __syncthreads();  // the block's reads are done, and Wl is there
+    if (!herm) {
+        const int at = MODE == 2 && outer ? kNsdNb : 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int t = T0 + 4 * r + lk;
+            if (live && t < nb) {
+                Am[(size_t)g * n + ks + t] = make_double2(-re[r], -im[r]);
+                double2 *x = Am + (size_t)(ks + t) * n + g;
+                R[(size_t)(at + t) * n + g] = *x;
+                *x = make_double2(0.0, 0.0);
+            }
+        }
+        return;
+    }
+    if (MODE == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int t = T0 + 4 * r + lk;
+            if (live && t < nb) {
+                Am[(size_t)(ks + t) * n + g] = make_double2(re[r], im[r]);
+                if (low) Am[(size_t)g * n + ks + t] = make_double2(re[r], -im[r]);
+            }
+        }
+        return;
+    }
+    // the second product: MODE 1 R2 - D21 W1, MODE 2 W1 - (D1 D12) W2 (in every lane: the
+    // a of a lane past n is other lanes' operand)
+    double4_t re2 = {0.0, 0.0, 0.0, 0.0}, im2 = {0.0, 0.0, 0.0, 0.0};
+    const bool in1 = g0 >= k && g0 < K2, in2 = g0 >= K2 && g0 < ke;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int t = T0 + 4 * r + lk;
+        double2 x = make_double2(0.0, 0.0);
+        if (MODE == 1) {
+            if (live && !in1 && t < nb2) {
+                x = low ? Am[(size_t)g * n + K2 + t] : Am[(size_t)(K2 + t) * n + g];
+                if (low) x.x = -x.x;
+                if (outer) R[(size_t)(kNsdNb + t) * n + g] = x;
+            }
+        } else if (live && !in2) {
+            x = Am[(size_t)(k + t) * n + g];
+        }
+        re2[r] = x.x;
+        im2[r] = x.y;
+    }
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+        const int t = 4 * s + lk;
+        double2 a = make_double2(0.0, 0.0);
+        if (MODE == 1) {
+            if (T0 + li < nb2) a = Am[(size_t)(k + t) * n + K2 + T0 + li];  // conj(D21)
+            a.x = -a.x;
+        } else {
+            if (t < nb2) a = R[(size_t)t * n + k + T0 + li];
+            a = make_double2(-a.x, -a.y);
+        }
+        cmfma(re2, im2, a, Wl[t * 16 + li]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int t = T0 + 4 * r + lk;
+        const double2 w = make_double2(re[r], im[r]), x = make_double2(re2[r], im2[r]);
+        if (!live) continue;
+        if (MODE == 1) {
+            if (t < nb2) Am[(size_t)(K2 + t) * n + g] = x;
+            if (in2) R[(size_t)(g - K2) * n + k + t] = w;
+            else if (!in1) Am[(size_t)(k + t) * n + g] = w;
+        } else {
+            Am[(size_t)(k + t) * n + g] = x;
+            if (low) Am[(size_t)g * n + k + t] = make_double2(x.x, -x.y);
+            if (t < nb2 && !in2) {
+                Am[(size_t)(K2 + t) * n + g] = w;
+                if (low) Am[(size_t)g * n + K2 + t] = make_double2(w.x, -w.y);
+            }
         }
     }
 }
 
-// Rows r0 .. r0 + nbr of the columns cs copied to Rs [nbr][m] and zeroed in A
-// (the save of k_gje_swap_save without interchanges), one row per blockIdx.y.
-__global__ __launch_bounds__(256) void k_nsd_save(double2 *__restrict__ A, int n, int r0, int nbr, GjeCols cs,
-                                                  double2 *__restrict__ Rs) {
-    const int mat = blockIdx.z, jr = blockIdx.y;
-    const int m = cs.count();
-    const int cp = blockIdx.x * 256 + threadIdx.x;
-    if (cp >= m) return;
-    double2 *a = A + (size_t)mat * n * n + (size_t)(r0 + jr) * n + cs.col(cp);
-    Rs[(size_t)mat * nbr * m + (size_t)jr * m + cp] = *a;
-    *a = make_double2(0.0, 0.0);
+// One T x T tile of A at (I0, J0) plus s (the product), columns below jend.
+template <int T, bool PLAIN>
+__device__ __forceinline__ void nsd_tile(double2 *__restrict__ Am, int n, const PqOp &P, const PqOp &Q, int nbr,
+                                         int I0, int J0, int jend, double s, PqLds<T> &lds) {
+    double4_t cre[T / 32][T / 32], cim[T / 32][T / 32];
+    double2 old[T / 32][T / 32][4];
+    pq_sums<T, false, PLAIN>(P, Q, nullptr, I0, J0, 0, nbr, cre, cim, lds, [&] {
+        pq_each<T>([&](int a, int b, int r, int i, int j) {
+            old[a][b][r] = make_double2(0.0, 0.0);
+            if (I0 + i < n && J0 + j < jend) old[a][b][r] = Am[(size_t)(I0 + i) * n + J0 + j];
+        });
+    });
+    pq_each<T>([&](int a, int b, int r, int i, int j) {
+        if (I0 + i < n && J0 + j < jend)
+            Am[(size_t)(I0 + i) * n + J0 + j] =
+                make_double2(fma(s, cre[a][b][r], old[a][b][r].x), fma(s, cim[a][b][r], old[a][b][r].y));
+    });
+}
+
+// General form, inside an outer block of two panels: A[:, c0 .. c0 + 63] += A[:, K] R,
+// the rows of R in Rs's columns c0 ...  Grid (64-row tiles, matrices).
+__global__ __launch_bounds__(256) void k_nsd_inner(double2 *__restrict__ A, int n, int ks, int nb, int c0, int c1,
+                                                   const double2 *__restrict__ Rs, int nbo,
+                                                   const double *__restrict__ chk) {
+    __shared__ PqLds<64> lds;
+    if (nsd_hermitian(chk, blockIdx.y)) return;
+    double2 *Am = A + (size_t)blockIdx.y * n * n;
+    nsd_tile<64, true>(Am, n, {Am + ks, n, n}, {Rs + (size_t)blockIdx.y * nbo * n, n, c1}, nb, 64 * blockIdx.x, c0, c1,
+                       1.0, lds);
+}
+
+// Bands of 8 tile rows, columns from the band's first row on: item u of a matrix.
+__host__ __device__ inline int nsd_items(int nt) {
+    int m = 0;
+    for (int b = 0; b < nt; b += 8) m += 8 * (nt - b);
+    return m;
+}
+
+// Rank-nbr update by outer block O = [k, ke) of everything outside it.  Hermitian: with W
+// in rows O of A and R in Rs, tiles on and above the diagonal: A[i, j] -+= conj(W[:,
+// i]) R[:, j] (+ for rows before O, whose part of column O has changed sign).
+// General: A[:, j] += A[:, O] R[:, j].  Grid (items, a multiple of 8; matrices): an
+// XCD takes a contiguous eighth of a matrix's bands, so that the panels its blocks
+// share stay in its L2.
+template <int T>
+__global__ __launch_bounds__(256, 2) void k_nsd_update(double2 *__restrict__ A, int n, int k, int ke,
+                                                       const double2 *__restrict__ Rs, int nbo,
+                                                       const double *__restrict__ chk) {
+    __shared__ PqLds<T> lds;
+    constexpr int SUB = 64 / T;
+    const int nt = (n + 63) / 64;
+    double2 *Am = A + (size_t)blockIdx.y * n * n;
+    const PqOp Q = {Rs + (size_t)blockIdx.y * nbo * n, n, n};
+    const int per = gridDim.x / 8;
+    if (nsd_hermitian(chk, blockIdx.y)) {
+        const int item = (blockIdx.x % 8) * per + blockIdx.x / 8;
+        int u = item / (SUB * SUB), b = 0;
+        const int sub = item % (SUB * SUB);
+        while (b < nt && u >= 8 * (nt - b)) {
+            u -= 8 * (nt - b);
+            b += 8;
+        }
+        const int I0 = (b + u % 8) * 64 + T * (sub / SUB), J0 = (b + u / 8) * 64 + T * (sub % SUB);
+        if (b >= nt || I0 / 64 > J0 / 64 || I0 >= n || J0 >= n) return;
+        if ((I0 >= k && I0 < ke) || (J0 >= k && J0 < ke)) return;
+        nsd_tile<T, false>(Am, n, {Am + (size_t)k * n, n, n}, Q, ke - k, I0, J0, n, I0 < k ? 1.0 : -1.0, lds);
+        return;
+    }
+    const int nT = (n + T - 1) / T;
+    for (int u = blockIdx.x; u < nT * nT; u += gridDim.x) {
+        const int I0 = (u % nT) * T, J0 = (u / nT) * T;
+        if (J0 >= k && J0 < ke) continue;
+        nsd_tile<T, true>(Am, n, {Am + k, n, n}, Q, ke - k, I0, J0, n, 1.0, lds);
+    }
 }
 
 namespace {
@@ -1315,35 +1638,61 @@ int launch_nsd_check(const double2 *chi, const double *v, int n, int nall, int n
     return BGW_OK;
 }
 
-// Rank-nbr update of the columns cs by the panel [r0, r0 + nbr), no interchanges.
-static int nsd_apply(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, double2 *Rs, hipStream_t st) {
-    const int m = cs.count();
-    if (m <= 0) return BGW_OK;
-    hipLaunchKernelGGL(k_nsd_save, dim3((m + 255) / 256, nbr, nmat), dim3(256), 0, st, A, n, r0, nbr, cs, Rs);
-    launch_gje_update(A, n, nmat, r0, nbr, cs, Rs, st);
+// epst or eps of every matrix (chi and out may be the same), after the check.
+int launch_nsd_build(const double2 *chi, const double *v, int n, int nall, int nmat, double2 *out, void *ws,
+                     hipStream_t st) {
+    NsdWs w = nsd_layout(ws, n, nmat, nall);
+    for (int m0 = 0; m0 < nall; m0 += 65535) {
+        const int mm = std::min(65535, nall - m0);
+        hipLaunchKernelGGL(k_nsd_build, dim3(n, mm), dim3(256), 0, st, chi + (size_t)m0 * n * n, v, n,
+                           (const double *)w.chk + 2 * (size_t)m0, out + (size_t)m0 * n * n);
+    }
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
 
+template <int T>
+static void launch_nsd_update(double2 *A, int n, int nmat, int k, int ke, const double2 *Rs, int nbo,
+                              const double *chk, hipStream_t st) {
+    const int items = nsd_items((n + 63) / 64) * (64 / T) * (64 / T);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_nsd_update<T>), dim3((items + 7) / 8 * 8, nmat), dim3(256), 0, st, A, n, k, ke,
+                       Rs, nbo, chk);
+}
+
 // In place: A[nmat][n][n] (matrices m0 .. m0 + nmat of the checked set).
-int launch_nsd_invert(double2 *A, int n, int nmat, int m0, int nall, int *info, void *ws, hipStream_t st) {
+int launch_nsd_invert(double2 *A, const double *v, int n, int nmat, int m0, int nall, int *info, void *ws,
+                      hipStream_t st) {
     NsdWs w = nsd_layout(ws, n, nmat, nall);
     const double *chk = w.chk + 2 * (size_t)m0;
+    double2 *Rs = w.Rs;
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, (unsigned int *)info, (size_t)nmat, 0u);
-    const size_t rlds = sizeof(double2) * ((size_t)kNsdNb * kNsdNb + (size_t)kNsdRowsPer * (kNsdNb + 1));
-    BGW_HIP(hipFuncSetAttribute((const void *)k_nsd_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rlds));
     const int nbo = gje_outer_nb(n);
+    const dim3 rg((n + 15) / 16, nmat), dg(nmat), t256(256), tdiag(kNsdDiagThreads), ig((n + 63) / 64, nmat);
+    const int nt = (n + 63) / 64;
+    // 64-wide tiles from eight per CU on, as for k_gje_update: one matrix of 1500 (300
+    // of them) 1.45 ms in 64-wide and 1.38 in 32-wide tiles, four of 4000 (8064) 22.8 and 24.2
+    const bool wide = (long long)nmat * nt * (nt + 1) / 2 >= 2000;
     for (int k = 0; k < n; k += nbo) {
-        const int ke = std::min(n, k + nbo);
-        for (int ks = k; ks < ke; ks += kNsdNb) {
-            const int nb = std::min(kNsdNb, ke - ks);
-            hipLaunchKernelGGL(k_nsd_diag, dim3(nmat), dim3(kNsdDiagThreads), 0, st, A, n, ks, nb, w.Dinv, chk, info);
-            hipLaunchKernelGGL(k_nsd_rows, dim3((n + kNsdRowsPer - 1) / kNsdRowsPer, nmat), dim3(256), rlds, st, A, n,
-                               ks, nb, (const double2 *)w.Dinv);
-            BGW_TRY(nsd_apply(A, n, nmat, ks, nb, GjeCols{k, ke, ks, ks + nb}, w.Rs, st));
+        const int ke = std::min(n, k + nbo), K2 = k + kNsdNb;
+        const int nb = std::min(kNsdNb, ke - k), nb2 = ke - K2;
+        hipLaunchKernelGGL(k_nsd_diag, dg, tdiag, 0, st, A, n, k, nb, w.Dinv, chk, info);
+        if (nb2 <= 0) {
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_nsd_rows<0>), rg, t256, 0, st, A, n, k, ke, k, nb, w.Dinv, Rs, nbo, chk);
+        } else {
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_nsd_rows<1>), rg, t256, 0, st, A, n, k, ke, k, nb, w.Dinv, Rs, nbo, chk);
+            hipLaunchKernelGGL(k_nsd_inner, ig, t256, 0, st, A, n, k, nb, K2, ke, Rs, nbo, chk);
+            hipLaunchKernelGGL(k_nsd_diag, dg, tdiag, 0, st, A, n, K2, nb2, w.Dinv, chk, info);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_nsd_rows<2>), rg, t256, 0, st, A, n, k, ke, K2, nb2, w.Dinv, Rs, nbo,
+                               chk);
+            hipLaunchKernelGGL(k_nsd_inner, ig, t256, 0, st, A, n, K2, nb2, k, K2, Rs, nbo, chk);
         }
-        BGW_TRY(nsd_apply(A, n, nmat, k, ke - k, GjeCols{0, n, k, ke}, w.Rs, st));
+        if (n > ke - k) {
+            if (wide) launch_nsd_update<64>(A, n, nmat, k, ke, Rs, nbo, chk, st);
+            else launch_nsd_update<32>(A, n, nmat, k, ke, Rs, nbo, chk, st);
+        }
     }
+    const int tiles = (n + kNsdTile - 1) / kNsdTile;
+    hipLaunchKernelGGL(k_nsd_unscale, dim3(tiles * (tiles + 1) / 2, nmat), t256, 0, st, A, v, n, tiles, chk);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
