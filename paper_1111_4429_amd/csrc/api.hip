@@ -529,9 +529,14 @@ static int plan_pair(bgw_handle_t h, const bgw_pair_desc *d, PairRun &R) {
     R.ncb = ncb;
     const size_t t_bytes_for = two_pass ? t_per_pair * (size_t)d->nv * ncb : 0;  // per k in the batch
     // x-stick results of the lane-per-line band path, reused by the valence and conduction launches
-    const bool band_lines = !generic_fft() && band_lines_supported(px, py, pz, pl->sm);
+    // (at 48^3 the one-kernel band path is the alternative, which needs none: they lie in T's place, which is
+    // free until the pairs, or not at all)
+    const size_t w_lines = band_lines_bytes(px, py, pz, pl->sm, std::max(d->nv, d->nc));
+    const bool w_in_t = pz.n == 48;
+    const bool band_lines = !generic_fft() && band_lines_supported(px, py, pz, pl->sm) &&
+                            (!w_in_t || (two_pass && w_lines <= t_bytes_for));
     R.band_lines = band_lines;
-    const size_t w_per_k = band_lines ? band_lines_bytes(px, py, pz, pl->sm, std::max(d->nv, d->nc)) : 0;
+    const size_t w_per_k = band_lines && !w_in_t ? w_lines : 0;
     int kb = (int)std::min<size_t>((size_t)d->nk, budget / (per_k + t_bytes_for + w_per_k + 1));
     if (kb < 1) return fail(BGW_ERR_NOMEM, "workspace for one k-point of band grids does not fit");
     if (two_pass) kb = (int)std::min<size_t>((size_t)kb, std::max<size_t>(1, t_cap / (t_per_pair * d->nv * ncb)));
@@ -540,6 +545,7 @@ static int plan_pair(bgw_handle_t h, const bgw_pair_desc *d, PairRun &R) {
     R.t_off = ((grid_bytes + 255) / 256) * 256;
     R.w_off = R.t_off + ((two_pass ? t_bytes_for * kb : 0) + 255) / 256 * 256;
     R.ws_need = R.w_off + w_per_k * kb;
+    if (w_in_t) R.w_off = R.t_off;
     return BGW_OK;
 }
 

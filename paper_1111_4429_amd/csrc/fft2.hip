@@ -203,6 +203,8 @@ template <>
 struct LineDFT<24> : RegFFT2<8, 3> {};
 template <>
 struct LineDFT<32> : RegFFT2<8, 4> {};
+template <>
+struct LineDFT<48> : RegFFT2<16, 3> {};
 
 // n = R1 * R2; element z of a line at line[z * es].  Stage 1 (in place): for
 // each za < R2, Y_za = DFT_R1 over x[za + R2 zb], times w_n^{za kb}, stored at
@@ -360,8 +362,8 @@ __global__ __launch_bounds__(NT) void k_pair_yz(const double2 *__restrict__ gv, 
 }
 
 // Pass A for y and z lengths N <= 32, one wavefront per workgroup and no
-// workgroup barriers.  Workgroup = (k, c, block of x-planes); it loops over
-// the valence bands and takes G x-planes of one pair per round:
+// workgroup barriers.  Workgroup = (k, c, block of x-planes, block of valence
+// bands); it loops over the bands and takes G x-planes of one pair per round:
 //   y: lane (plane p, z) reads the y-line of u_v and u_c at that z (at fixed y
 //      the lanes of one plane read N consecutive elements: coalesced),
 //      forms conj(u_v) u_c, does the whole N-point DFT in registers and
@@ -374,17 +376,20 @@ __global__ __launch_bounds__(NT) void k_pair_yz(const double2 *__restrict__ gv, 
 template <int N, int G, int MINW>
 __global__ __launch_bounds__(64, MINW) void k_pair_yzr(const double2 *__restrict__ gv, const double2 *__restrict__ gc,
                                                  int nv, int nc, int c0, int ncb, int n1, int rey, int rez, int xblk,
-                                                 double2 *__restrict__ T) {
+                                                 int vblk, double2 *__restrict__ T) {
     constexpr int QS = N + 1;
     extern __shared__ double2 Q[];  // [G][bey][QS]
     const int lane = threadIdx.x;
     const int bey = 2 * rey + 1, bez = 2 * rez + 1, nbox = bey * bez;
     const int nxb = (n1 + xblk - 1) / xblk;
     const int cl = blockIdx.x % ncb;
-    const int rest = blockIdx.x / ncb;
+    const int nvb = (nv + vblk - 1) / vblk;
+    int rest = blockIdx.x / ncb;
     const int xb = rest % nxb;
-    const int k = rest / nxb;
-    const int x0 = xb * xblk, x1 = min(n1, x0 + xblk);
+    rest /= nxb;
+    const int vb = rest % nvb;
+    const int k = rest / nvb;
+    const int x0 = xb * xblk, x1 = min(n1, x0 + xblk), v0 = vb * vblk, v1 = min(nv, v0 + vblk);
     const size_t plane = (size_t)N * N;
     const size_t NB = (size_t)n1 * plane;
     const double2 *uc = gc + (size_t)(k * nc + c0 + cl) * NB;
@@ -392,7 +397,7 @@ __global__ __launch_bounds__(64, MINW) void k_pair_yzr(const double2 *__restrict
     const int py = lane / N, zl = lane - py * N;   // y-stage role
     const int pz = lane / bey, iy = lane - pz * bey;  // z-stage role
 #pragma unroll 1
-    for (int v = 0; v < nv; ++v) {
+    for (int v = v0; v < v1; ++v) {
         const long long tl = ((long long)k * nv + v) * ncb + cl;
 #pragma unroll 1
         for (int xg = x0; xg < x1; xg += G) {
@@ -825,6 +830,19 @@ __global__ __launch_bounds__(64) void k_band_yz(const double2 *__restrict__ W, i
 // ------------------------------------------------------------------ host side
 
 namespace {
+// x-planes per workgroup of a pass: up to `rounds` rounds of G (fewer workgroups to
+// start, longer streams) while that leaves `wgs` workgroups, for the lane-per-line
+// passes the eight per CU that their registers allow; else fewer rounds, and in
+// pass A then fewer valence bands per workgroup.  128 conduction times 64 valence
+// bands on 32^3: 512 workgroups 1531 us, 2048 941 us; 16 times 4 on 16^3: 16
+// workgroups 34 us, 64 9.7 us.
+constexpr long long kLineWgs = 2048;
+int lines_xblk(int n1, int G, long long per_block, int rounds = 4, long long wgs = kLineWgs) {
+    int r = std::max(1, std::min((n1 + G - 1) / G, rounds));
+    while (r > 1 && per_block * ((n1 + r * G - 1) / (r * G)) < wgs) --r;
+    return r * G;
+}
+
 template <int Z1, int Z2, int LC>
 int launch_pair_yz_t(const double2 *gv, const double2 *gc, int nkb, int nv, int nc, int c0, int ncb,
                      const AxisPlan &px, const AxisPlan &py, const AxisPlan &pz, int rey, int rez, double2 *T,
@@ -837,7 +855,10 @@ int launch_pair_yz_t(const double2 *gv, const double2 *gc, int nkb, int nv, int 
     auto kern = k_pair_yz<Z1, Z2, 256, LC>;
     BGW_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const int n1 = px.n;
-    const int xblk = std::max(1, std::min(n1, 8));
+    // up to eight planes per workgroup while eight rounds of the two workgroups that a
+    // CU holds are left: 151 conduction times 32 valence bands on 48^3, 906 workgroups
+    // of eight planes 3.01 ms, 1812 of four 2.72, 7248 of one 2.53
+    const int xblk = lines_xblk(n1, 1, (long long)nkb * ncb, 8, 4096);
     const int nxb = (n1 + xblk - 1) / xblk;
     const long long grid = (long long)nkb * nxb * ncb;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, st, gv, gc, nkb, nv, nc, c0, ncb, n1, py.tw, pz.tw,
@@ -861,6 +882,19 @@ int launch_pair_x_t(const double2 *T, long long npairs, const AxisPlan &px, int 
     return BGW_OK;
 }
 
+// Workgroups along x and along the valence bands of one launch.
+struct LineGrid {
+    int xblk, vblk;
+    long long wgs;
+    LineGrid(int n1, int G, int nkb, int ncb, int nv) {
+        xblk = lines_xblk(n1, G, (long long)nkb * ncb);
+        const long long per_v = (long long)nkb * ncb * ((n1 + xblk - 1) / xblk);
+        vblk = nv;
+        while (vblk > 1 && per_v * ((nv + vblk - 1) / vblk) < kLineWgs) vblk = (vblk + 1) / 2;
+        wgs = per_v * ((nv + vblk - 1) / vblk);
+    }
+};
+
 template <int N, int G, int MINW>
 int launch_pair_yzr_t(const double2 *gv, const double2 *gc, int nkb, int nv, int nc, int c0, int ncb, int n1,
                       int rey, int rez, double2 *T, hipStream_t st) {
@@ -869,10 +903,9 @@ int launch_pair_yzr_t(const double2 *gv, const double2 *gc, int nkb, int nv, int
     const size_t lds = sizeof(double2) * (size_t)G * bey * (N + 1);
     auto kern = k_pair_yzr<N, G, MINW>;
     BGW_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const int xblk = std::max(G, std::min(n1, 4 * G));
-    const int nxb = (n1 + xblk - 1) / xblk;
-    const long long grid = (long long)nkb * nxb * ncb;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64), lds, st, gv, gc, nv, nc, c0, ncb, n1, rey, rez, xblk, T);
+    const LineGrid g(n1, G, nkb, ncb, nv);
+    hipLaunchKernelGGL(kern, dim3((unsigned)g.wgs), dim3(64), lds, st, gv, gc, nv, nc, c0, ncb, n1, rey, rez, g.xblk,
+                       g.vblk, T);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
@@ -1036,8 +1069,8 @@ size_t band_lines_bytes(const AxisPlan &px, const AxisPlan &py, const AxisPlan &
 
 bool band_lines_supported(const AxisPlan &px, const AxisPlan &py, const AxisPlan &pz, const SphereMaps &sm) {
     if (px.n != py.n || py.n != pz.n || !sm.sticks_contiguous) return false;
-    const int n = pz.n, G = n == 16 ? 4 : 2;
-    return (n == 16 || n == 24 || n == 32) && G * (2 * sm.rwy + 1) <= 64;
+    const int n = pz.n, G = n == 16 ? 4 : n == 48 ? 1 : 2;
+    return (n == 16 || n == 24 || n == 32 || n == 48) && G * (2 * sm.rwy + 1) <= 64;
 }
 
 namespace {
@@ -1051,7 +1084,7 @@ int launch_band_lines_t(const double2 *C, int nbands, int ngw, const SphereMaps 
     const size_t lds = sizeof(double2) * (size_t)G * bwy * (N + 1);
     auto kern = k_band_yz<N, G>;
     BGW_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const int xblk = 4 * G;
+    const int xblk = lines_xblk(N, G, nbands);
     const int nxb = (N + xblk - 1) / xblk;
     hipLaunchKernelGGL(kern, dim3((unsigned)((long long)nbands * nxb)), dim3(64), lds, st, W, sm.ncell, sm.rwy,
                        sm.rwz, xblk, grids);
@@ -1068,6 +1101,7 @@ int launch_band_lines(const double2 *C, int nbands, int ngw, const AxisPlan &px,
         case 16: return launch_band_lines_t<16, 4>(C, nbands, ngw, sm, W, grids, st);
         case 24: return launch_band_lines_t<24, 2>(C, nbands, ngw, sm, W, grids, st);
         case 32: return launch_band_lines_t<32, 2>(C, nbands, ngw, sm, W, grids, st);
+        case 48: return launch_band_lines_t<48, 1>(C, nbands, ngw, sm, W, grids, st);
         default: return BGW_ERR_UNSUPPORTED;
     }
 }
