@@ -47,10 +47,15 @@ __host__ __device__ inline double2 cscale(double2 a, double s) { return make_dou
 // A pointer read from a device table, as one to global memory: the compiler
 // otherwise emits flat loads and stores, which count against the LDS waits too.
 typedef __attribute__((address_space(1))) double2 global_double2;
+typedef __attribute__((address_space(1))) double global_double;
 typedef __attribute__((address_space(1))) int global_int;
 __device__ inline const global_double2 *as_global(const double2 *p) { return (const global_double2 *)p; }
 __device__ inline global_double2 *as_global(double2 *p) { return (global_double2 *)p; }
+__device__ inline const global_double *as_global(const double *p) { return (const global_double *)p; }
+__device__ inline global_double *as_global(double *p) { return (global_double *)p; }
 __device__ inline const global_int *as_global(const int *p) { return (const global_int *)p; }
+
+constexpr int kFinTile = 32;  // tiles in which the finalize kernels write a matrix and its mirror
 
 // ---------------------------------------------------------------- FFT plans
 // One axis of a 3D transform: length n = product of radices (each 2, 3 or 4),
