@@ -444,29 +444,88 @@ struct GjeCols {
     }
 };
 
-// For every column of cs: apply the interchanges ipiv[r0 .. r0+nbr) in order
-// (none when ipiv is null), copy rows r0 .. r0+nbr-1 to Rs [nbr][m] and zero
-// them in A.
-__global__ __launch_bounds__(64) void k_gje_swap_save(double2 *__restrict__ A, int n, int r0, int nbr, GjeCols cs,
-                                                      const int *__restrict__ ipiv, double2 *__restrict__ Rs) {
-    const int mat = blockIdx.y;
+constexpr int kSwapCols = 32;     // columns of one k_gje_swap_save workgroup
+constexpr int kSwapRows = 4 * kPanelMax;
+
+// Row interchanges ipiv[r0 .. r0+nbr) on the columns cs, then the panel's rows r0 ..
+// copied to Rs [nbr][m] and zeroed in A.  One after the other the interchanges are a
+// chain of nbr round trips to memory per column; here wave 0 first plays them on
+// row numbers held in its lanes (slot j: panel row r0 + j; slot 128 + j: the row
+// outside the panel that interchange j names, at its first naming), and then every
+// row moves once, independent of the others.  Eight matrices of 1500, 24 outer blocks
+// of 64 rows and 94 panels of 16: 1.67 -> 0.95 ms in all.  256 threads: 32 columns
+// times 8 groups of rows; nbr <= 128.
+__global__ __launch_bounds__(256) void k_gje_swap_save(double2 *__restrict__ A, int n, int r0, int nbr, GjeCols cs,
+                                                       const int *__restrict__ ipiv, double2 *__restrict__ Rs) {
+    __shared__ int piv[kSwapRows], slot[kSwapRows], from[2 * kSwapRows];
+    extern __shared__ double2 out[];  // [nbr][kSwapCols]: new contents of the outside rows
+    const int mat = blockIdx.y, tid = threadIdx.x;
     double2 *Am = A + (size_t)mat * n * n;
-    const int *ip = ipiv ? ipiv + (size_t)mat * n : nullptr;
     const int m = cs.count();
     double2 *R = Rs + (size_t)mat * nbr * m;
-    for (int cp = blockIdx.x * blockDim.x + threadIdx.x; cp < m; cp += gridDim.x * blockDim.x) {
-        const int c = cs.col(cp);
-        for (int j = 0; ip && j < nbr; ++j) {
-            const int p = ip[r0 + j];
-            if (p > r0 + j && p < n) {
-                const double2 t = Am[(size_t)(r0 + j) * n + c];
-                Am[(size_t)(r0 + j) * n + c] = Am[(size_t)p * n + c];
-                Am[(size_t)p * n + c] = t;
-            }
+    if (tid < nbr) {
+        const int p = ipiv[(size_t)mat * n + r0 + tid];
+        piv[tid] = p > r0 + tid && p < n ? p : r0 + tid;  // anything else: no interchange
+    }
+    __syncthreads();
+    if (tid < nbr) {
+        const int p = piv[tid];
+        int s = p - r0;
+        if (s >= nbr) {
+            int j = 0;
+            while (piv[j] != p) ++j;
+            s = kSwapRows + j;
+        }
+        slot[tid] = s;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // row numbers in slots lane, 64 + lane, 128 + lane, 192 + lane
+        int c[4], q[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = 64 * h + tid;
+            c[h] = r0 + j;
+            c[2 + h] = j < nbr ? piv[j] : 0;
+            q[h] = j < nbr ? slot[j] : j;
         }
         for (int j = 0; j < nbr; ++j) {
-            R[(size_t)j * m + cp] = Am[(size_t)(r0 + j) * n + c];
-            Am[(size_t)(r0 + j) * n + c] = make_double2(0.0, 0.0);
+            const int lj = j & 63;
+            const int s = __builtin_amdgcn_readlane(j < 64 ? q[0] : q[1], lj), ls = s & 63;
+            const int x = __builtin_amdgcn_readlane(j < 64 ? c[0] : c[1], lj);
+            int y = 0;
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                if (s >> 6 == h) {
+                    y = __builtin_amdgcn_readlane(c[h], ls);
+                    if (tid == ls) c[h] = x;
+                }
+            if (tid == lj) {
+                if (j < 64) c[0] = y;
+                else c[1] = y;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 4; ++h) from[64 * h + tid] = c[h];
+    }
+    __syncthreads();
+    const int cl = tid % kSwapCols, rg = tid / kSwapCols, cp = blockIdx.x * kSwapCols + cl;
+    const bool live = cp < m;
+    const int col = live ? cs.col(cp) : 0;
+    constexpr int NG = 256 / kSwapCols;
+    if (live) {
+#pragma unroll 4
+        for (int j = rg; j < nbr; j += NG) {
+            R[(size_t)j * m + cp] = Am[(size_t)from[j] * n + col];
+            if (slot[j] == kSwapRows + j) out[j * kSwapCols + cl] = Am[(size_t)from[kSwapRows + j] * n + col];
+        }
+    }
+    __syncthreads();
+    if (live) {
+#pragma unroll 4
+        for (int j = rg; j < nbr; j += NG) {
+            Am[(size_t)(r0 + j) * n + col] = make_double2(0.0, 0.0);
+            if (slot[j] == kSwapRows + j) Am[(size_t)piv[j] * n + col] = out[j * kSwapCols + cl];
         }
     }
 }
@@ -885,7 +944,9 @@ static int gje_apply(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, c
                      hipStream_t st) {
     const int m = cs.count();
     if (m <= 0) return BGW_OK;
-    hipLaunchKernelGGL(k_gje_swap_save, dim3((m + 63) / 64, nmat), dim3(64), 0, st, A, n, r0, nbr, cs, ipiv, Rs);
+    const size_t lds = sizeof(double2) * (size_t)nbr * kSwapCols;
+    hipLaunchKernelGGL(k_gje_swap_save, dim3((m + kSwapCols - 1) / kSwapCols, nmat), dim3(256), lds, st, A, n, r0, nbr, cs,
+                       ipiv, Rs);
     launch_gje_update(A, n, nmat, r0, nbr, cs, Rs, st);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
@@ -958,6 +1019,8 @@ int launch_gje_invert(double2 *A, int n, int nmat, int *info, void *ws, int *ipi
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, (unsigned int *)info, (size_t)nmat, 0u);
     BGW_HIP(hipGetLastError());
 
+    BGW_HIP(hipFuncSetAttribute((const void *)k_gje_swap_save, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(sizeof(double2) * kSwapRows * kSwapCols)));
     if (gje_one_wg(n)) {
         BGW_TRY(launch_gje_invert_wg(A, n, nmat, ipiv, info, Rs, st));
     } else {
