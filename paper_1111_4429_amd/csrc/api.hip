@@ -540,6 +540,8 @@ static int plan_pair(bgw_handle_t h, const bgw_pair_desc *d, PairRun &R) {
     int kb = (int)std::min<size_t>((size_t)d->nk, budget / (per_k + t_bytes_for + w_per_k + 1));
     if (kb < 1) return fail(BGW_ERR_NOMEM, "workspace for one k-point of band grids does not fit");
     if (two_pass) kb = (int)std::min<size_t>((size_t)kb, std::max<size_t>(1, t_cap / (t_per_pair * d->nv * ncb)));
+    // equal batches: 64 k-points of 1600 pairs on 24^3 as 62 + 2 left the chip idle in the second
+    kb = (d->nk + (d->nk + kb - 1) / kb - 1) / ((d->nk + kb - 1) / kb);
     R.kb = kb;
     const size_t grid_bytes = per_k * kb;
     R.t_off = ((grid_bytes + 255) / 256) * 256;
