@@ -36,10 +36,9 @@ int launch_pair_yz(const double2 *gv, const double2 *gc, int nkb, int nv, int nc
                    const AxisPlan &px, const AxisPlan &py, const AxisPlan &pz, int rey, int rez, double2 *T,
                    hipStream_t st);
 int launch_pair_yzr(const double2 *gv, const double2 *gc, int nkb, int nv, int nc, int c0, int ncb,
-                    const AxisPlan &px, const AxisPlan &py, const AxisPlan &pz, int rey, int rez, double2 *T,
+                    const AxisPlan &px, const AxisPlan &py, const AxisPlan &pz, const SphereMaps &sm, double2 *T,
                     hipStream_t st);
-int launch_pair_x(const double2 *T, long long npairs, const AxisPlan &px, int rey, int rez, const int *ge_code2,
-                  const int *ge_out, int ng, double2 *M, int nv, int nc, int c0, int ncb, long long row0, size_t N,
+int launch_pair_x(const double2 *T, long long npairs, const AxisPlan &px, const SphereMaps &sm, int ng, double2 *M, int nv, int nc, int c0, int ncb, long long row0, size_t N,
                   bool yfast, hipStream_t st);
 int launch_band_to_real2(const double2 *C, int nbands, int ngw, const AxisPlan &, const AxisPlan &,
                          const AxisPlan &, const SphereMaps &, int rwy, double2 *grids, hipStream_t);
@@ -391,6 +390,25 @@ static int get_plan(bgw_handle_t h, const bgw_pair_desc *d, FFTPlan **out) {
         rez = std::max(rez, std::abs(d->ge[3 * g + 2]));
         rey = std::max(rey, std::abs(d->ge[3 * g + 1]));
     }
+    std::vector<int> ylo((size_t)(2 * rez + 1), 2 * rey + 1), yhi((size_t)(2 * rez + 1), -1), trow;
+    for (int g = 0; g < d->ng; ++g) {
+        const size_t iz = (size_t)(d->ge[3 * g + 2] + rez);
+        ylo[iz] = std::min(ylo[iz], d->ge[3 * g + 1] + rey);
+        yhi[iz] = std::max(yhi[iz], d->ge[3 * g + 1] + rey);
+    }
+    if (n2 >= 32) {  // the whole box (k_pair_yzr)
+        std::fill(ylo.begin(), ylo.end(), 0);
+        std::fill(yhi.begin(), yhi.end(), 2 * rey);
+    }
+    sm.t_cols = 0;
+    for (size_t iz = 0; iz < ylo.size(); ++iz) {
+        const bool any = ylo[iz] <= yhi[iz];
+        trow.push_back(any ? sm.t_cols - ylo[iz] : 0);
+        trow.push_back(any ? ylo[iz] | (yhi[iz] << 16) : 1);  // no points: from 1 to 0
+        if (any) sm.t_cols += yhi[iz] - ylo[iz] + 1;
+    }
+    BGW_TRY(upload(*pl, trow.data(), sizeof(int) * trow.size(), &dp));
+    sm.t_row = (const int *)dp;
     std::vector<int> code((size_t)d->ng), code2((size_t)d->ng), order((size_t)d->ng);
     for (int g = 0; g < d->ng; ++g) {
         code[(size_t)g] = mod(d->ge[3 * g], n1) | (mod(d->ge[3 * g + 1], n2) << 8) | ((d->ge[3 * g + 2] + rez) << 16);
@@ -609,7 +627,7 @@ extern "C" int bgw_pair_density(bgw_handle_t h, const bgw_pair_desc *d, double *
                 bool yfast = true;
                 {
                     Timed tm(h, BGW_KERNEL_PAIR, st);
-                    int rc = launch_pair_yzr(gv, gc, kn, d->nv, d->nc, c0, cn, px, py, pz, pl->sm.rey, pl->sm.rez, T, st);
+                    int rc = launch_pair_yzr(gv, gc, kn, d->nv, d->nc, c0, cn, px, py, pz, pl->sm, T, st);
                     if (rc == BGW_ERR_UNSUPPORTED) {
                         yfast = false;
                         rc = launch_pair_yz(gv, gc, kn, d->nv, d->nc, c0, cn, px, py, pz, pl->sm.rey, pl->sm.rez, T, st);
@@ -617,8 +635,7 @@ extern "C" int bgw_pair_density(bgw_handle_t h, const bgw_pair_desc *d, double *
                     BGW_TRY(rc);
                 }
                 Timed tm(h, BGW_KERNEL_PAIR_X, st);
-                BGW_TRY(launch_pair_x(T, (long long)kn * d->nv * cn, px, pl->sm.rey, pl->sm.rez, pl->sm.ge_code2,
-                                      pl->sm.ge_out, d->ng, (double2 *)M, d->nv, d->nc, c0, cn, row0, N, yfast, st));
+                BGW_TRY(launch_pair_x(T, (long long)kn * d->nv * cn, px, pl->sm, d->ng, (double2 *)M, d->nv, d->nc, c0, cn, row0, N, yfast, st));
             }
         } else {
             Timed tm(h, BGW_KERNEL_PAIR, st);

@@ -87,6 +87,10 @@ struct SphereMaps {
     const int *ge_code;
     const int *ge_code2;   // (mx mod n1) | ((my + Rey) << 8) | ((mz + Rez) << 16), in (mx, my, mz) order
     const int *ge_out;     // original index of the p-th point of that order
+    // columns along x that pass A keeps (those that hold sphere points, or all), by rows iz = mz + Rez of consecutive iy = my + Rey: column
+    // (iy, iz) is number t_row[2 iz] + iy for iy from t_row[2 iz + 1] & 0xffff to t_row[2 iz + 1] >> 16
+    const int *t_row;
+    int t_cols;            // columns in all (those between two of a row's count)
     int bez, rez;          // dielectric box extent along z, Rez
     int rey;               // dielectric box half-extent along y
     // lane-per-line band path (x-sticks contiguous in mx): cell c = iz * bwy + iy

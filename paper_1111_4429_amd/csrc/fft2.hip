@@ -369,18 +369,25 @@ __global__ __launch_bounds__(NT) void k_pair_yz(const double2 *__restrict__ gv, 
 //      forms conj(u_v) u_c, does the whole N-point DFT in registers and
 //      stores the bey outputs of the dielectric box to Q[p][iy][z] in LDS;
 //   z: lane (plane p, iy) reads row Q[p][iy][.], does the N-point DFT in
-//      registers and writes the bez box outputs to T[t][x][iz][iy] (iy
-//      fastest, so the stores of a wave are contiguous runs).
+//      registers and writes the columns along x that hold sphere points to
+//      T[t][x][column] (iy fastest, so the stores of a wave are contiguous runs).
+// What bounds it on many pairs is memory: at 64 x 4 x 400 pairs of 1500 vectors
+// 11.5 GB read and 8.4 written at 4.2 TB/s (a large copy runs at 4.9), with the
+// box's corners, which hold no points, in T; without them (161 of 225 columns) the
+// pass took 4.99 -> 4.69 ms and pass B 2.26 -> 2.02.  Lines of 32 leave one wave per
+// SIMD, which the masked stores held up (0.94 -> 1.15 ms for 64 x 128 pairs): there
+// T keeps the whole box (t_row then says so).
 // The Q row stride N + 1 is odd in 16-byte units, so both the column writes
 // and the row reads are free of LDS bank conflicts.
 template <int N, int G, int MINW>
 __global__ __launch_bounds__(64, MINW) void k_pair_yzr(const double2 *__restrict__ gv, const double2 *__restrict__ gc,
                                                  int nv, int nc, int c0, int ncb, int n1, int rey, int rez, int xblk,
-                                                 int vblk, double2 *__restrict__ T) {
+                                                 int vblk, const int *__restrict__ t_row, int t_cols,
+                                                 double2 *__restrict__ T) {
     constexpr int QS = N + 1;
     extern __shared__ double2 Q[];  // [G][bey][QS]
     const int lane = threadIdx.x;
-    const int bey = 2 * rey + 1, bez = 2 * rez + 1, nbox = bey * bez;
+    const int bey = 2 * rey + 1;
     const int nxb = (n1 + xblk - 1) / xblk;
     const int cl = blockIdx.x % ncb;
     const int nvb = (nv + vblk - 1) / vblk;
@@ -460,11 +467,16 @@ __global__ __launch_bounds__(64, MINW) void k_pair_yzr(const double2 *__restrict
                 }
                 LineDFT<N>::run(e);
                 if (act) {
-                    double2 *o = T + ((size_t)tl * n1 + x) * nbox + iy;
+                    double2 *o = T + ((size_t)tl * n1 + x) * t_cols + iy;
 #pragma unroll
                     for (int kz = 0; kz < N; ++kz) {
                         const int m = kz <= N / 2 ? kz : kz - N;
-                        if (m >= -rez && m <= rez) o[(m + rez) * bey] = e[kz];
+                        if (N >= 32) {
+                            if (m >= -rez && m <= rez) o[(m + rez) * bey] = e[kz];
+                        } else if (m >= -rez && m <= rez) {
+                            const int at = t_row[2 * (m + rez)], span = t_row[2 * (m + rez) + 1];
+                            if (iy >= (span & 0xffff) && iy <= span >> 16) o[at] = e[kz];
+                        }
                     }
                 }
             }
@@ -475,15 +487,15 @@ __global__ __launch_bounds__(64, MINW) void k_pair_yzr(const double2 *__restrict
     }
 }
 
-// Pass B.  T: [npairs][n1][nbox], box point (iy, iz) at iy * ys + iz * zs;
-// sphere points in (mx, my, mz) order (ge_code2),
+// Pass B.  T: [npairs][n1][nbox], the whole box, iz fastest (t_row null), or the
+// columns that hold sphere points; sphere points in (mx, my, mz) order (ge_code2),
 // written back in the original order (ge_out).  XS planes staged per round.
 template <int ACC, int NT, int XS>
 __global__ __launch_bounds__(NT) void k_pair_x(const double2 *__restrict__ T, int n1, int nbox, int bez,
                                                const double2 *__restrict__ tw1g, const int *__restrict__ ge_code,
                                                const int *__restrict__ ge_out, int ng, double inv_n,
                                                double2 *__restrict__ M, int nv, int nc, int c0, int ncb,
-                                               long long m_row0, int ys, int zs) {
+                                               long long m_row0, const int *__restrict__ t_row) {
     extern __shared__ double2 lds[];
     double2 *tw1 = lds, *Ts = tw1 + n1;  // [XS][nbox]
     for (int i = threadIdx.x; i < n1; i += NT) tw1[i] = tw1g[i];
@@ -495,7 +507,8 @@ __global__ __launch_bounds__(NT) void k_pair_x(const double2 *__restrict__ T, in
     for (int i = 0; i < ACC; ++i) {
         const int g = threadIdx.x + i * NT;
         const int cd = g < ng ? ge_code[g] : -1;
-        slot[i] = cd >= 0 ? ((cd >> 8) & 0xff) * ys + (cd >> 16) * zs : -1;
+        const int iy = (cd >> 8) & 0xff, iz = cd >> 16;
+        slot[i] = cd < 0 ? -1 : t_row ? t_row[2 * iz] + iy : iy * bez + iz;
         mxs[i] = cd >= 0 ? (cd & 0xff) : 0;
         ph[i] = 0;
         acc[i] = make_double2(0.0, 0.0);
@@ -870,14 +883,14 @@ int launch_pair_yz_t(const double2 *gv, const double2 *gc, int nkb, int nv, int 
 template <int ACC>
 int launch_pair_x_t(const double2 *T, long long npairs, const AxisPlan &px, int nbox, int bez, const int *ge_code2,
                     const int *ge_out, int ng, double inv_n, double2 *M, int nv, int nc, int c0, int ncb,
-                    long long row0, int ys, int zs, hipStream_t st) {
+                    long long row0, const int *t_row, hipStream_t st) {
     constexpr int XS = 8;
     const size_t lds = sizeof(double2) * ((size_t)px.n + (size_t)XS * nbox);
     if (lds > 150 * 1024) return BGW_ERR_UNSUPPORTED;
     auto kern = k_pair_x<ACC, 256, XS>;
     BGW_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(kern, dim3((unsigned)npairs), dim3(256), lds, st, T, px.n, nbox, bez, px.tw, ge_code2, ge_out,
-                       ng, inv_n, M, nv, nc, c0, ncb, row0, ys, zs);
+                       ng, inv_n, M, nv, nc, c0, ncb, row0, t_row);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
@@ -897,15 +910,15 @@ struct LineGrid {
 
 template <int N, int G, int MINW>
 int launch_pair_yzr_t(const double2 *gv, const double2 *gc, int nkb, int nv, int nc, int c0, int ncb, int n1,
-                      int rey, int rez, double2 *T, hipStream_t st) {
-    const int bey = 2 * rey + 1;
+                      const SphereMaps &sm, double2 *T, hipStream_t st) {
+    const int rey = sm.rey, rez = sm.rez, bey = 2 * rey + 1;
     if (bey > N || 2 * rez + 1 > N || G * bey > 64) return BGW_ERR_UNSUPPORTED;
     const size_t lds = sizeof(double2) * (size_t)G * bey * (N + 1);
     auto kern = k_pair_yzr<N, G, MINW>;
     BGW_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const LineGrid g(n1, G, nkb, ncb, nv);
     hipLaunchKernelGGL(kern, dim3((unsigned)g.wgs), dim3(64), lds, st, gv, gc, nv, nc, c0, ncb, n1, rey, rez, g.xblk,
-                       g.vblk, T);
+                       g.vblk, sm.t_row, sm.t_cols, T);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
@@ -948,31 +961,30 @@ int launch_pair_yz(const double2 *gv, const double2 *gc, int nkb, int nv, int nc
 }
 
 // Pass A with one lane per line (y and z lengths 16, 24 or 32).  T then holds
-// each x-plane's box with iy fastest.  BGW_ERR_UNSUPPORTED when it does not apply.
+// the columns of SphereMaps::t_row.  BGW_ERR_UNSUPPORTED when it does not apply.
 int launch_pair_yzr(const double2 *gv, const double2 *gc, int nkb, int nv, int nc, int c0, int ncb,
-                    const AxisPlan &px, const AxisPlan &py, const AxisPlan &pz, int rey, int rez, double2 *T,
+                    const AxisPlan &px, const AxisPlan &py, const AxisPlan &pz, const SphereMaps &sm, double2 *T,
                     hipStream_t st) {
     if (py.n != pz.n) return BGW_ERR_UNSUPPORTED;
     switch (pz.n) {
-        case 16: return launch_pair_yzr_t<16, 4, 1>(gv, gc, nkb, nv, nc, c0, ncb, px.n, rey, rez, T, st);
-        case 24: return launch_pair_yzr_t<24, 2, 1>(gv, gc, nkb, nv, nc, c0, ncb, px.n, rey, rez, T, st);
-        case 32: return launch_pair_yzr_t<32, 2, 1>(gv, gc, nkb, nv, nc, c0, ncb, px.n, rey, rez, T, st);
+        case 16: return launch_pair_yzr_t<16, 4, 1>(gv, gc, nkb, nv, nc, c0, ncb, px.n, sm, T, st);
+        case 24: return launch_pair_yzr_t<24, 2, 1>(gv, gc, nkb, nv, nc, c0, ncb, px.n, sm, T, st);
+        case 32: return launch_pair_yzr_t<32, 2, 1>(gv, gc, nkb, nv, nc, c0, ncb, px.n, sm, T, st);
         default: return BGW_ERR_UNSUPPORTED;
     }
 }
 
-// yfast: T box points stored iy fastest (lane-per-line pass A), else iz fastest.
-int launch_pair_x(const double2 *T, long long npairs, const AxisPlan &px, int rey, int rez, const int *ge_code2,
-                  const int *ge_out, int ng, double2 *M, int nv, int nc, int c0, int ncb, long long row0, size_t N,
+// yfast: T as the lane-per-line pass A leaves it, else the whole box, iz fastest.
+int launch_pair_x(const double2 *T, long long npairs, const AxisPlan &px, const SphereMaps &sm, int ng, double2 *M, int nv, int nc, int c0, int ncb, long long row0, size_t N,
                   bool yfast, hipStream_t st) {
-    const int bez = 2 * rez + 1, bey = 2 * rey + 1, nbox = bey * bez;
-    const int ys = yfast ? 1 : bez, zs = yfast ? bey : 1;
+    const int bez = 2 * sm.rez + 1, nbox = yfast ? sm.t_cols : (2 * sm.rey + 1) * bez;
+    const int *t_row = yfast ? sm.t_row : nullptr, *ge_code2 = sm.ge_code2, *ge_out = sm.ge_out;
     const double inv_n = 1.0 / (double)N;
     const int per = (ng + 255) / 256;
 #define BGW_PX(A)                                                                                               \
     if (per <= A)                                                                                               \
         return launch_pair_x_t<A>(T, npairs, px, nbox, bez, ge_code2, ge_out, ng, inv_n, M, nv, nc, c0, ncb, row0, \
-                                  ys, zs, st);
+                                  t_row, st);
     BGW_PX(1)
     BGW_PX(2)
     BGW_PX(4)
