@@ -122,14 +122,15 @@ __global__ __launch_bounds__(256, 3) void k_herk_f64(const HerkProb *__restrict_
 // Without B (imaginary axis) chi is Hermitian and its diagonal exactly real.
 // In place (ns == 1, no B) chi's upper triangle holds the raw sums.  Row and
 // column `skip` (>= 0) are left untouched (written by the FP64 head kernel).
-// A block takes 32 x 32 tiles on or above the diagonal: it sums each element
+// A block takes 8 x 32 tiles on or above the diagonal: it sums each element
 // once and writes the mirror, in rows, through LDS (four matrices of 4000: 1.09 ms
 // with the mirror's sums read down the columns, 0.29 now).
 // grid.y: output matrix.
 __global__ __launch_bounds__(256) void k_chi_finalize(const FinProb *__restrict__ probs) {
-    __shared__ double2 tile[kFinTile][kFinTile + 1];
+    __shared__ double2 tile[kFinRows][kFinTile + 1];
     const FinProb P = probs[blockIdx.y];
-    const int ng = P.ng, nt = (ng + kFinTile - 1) / kFinTile, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int ng = P.ng, nt = (ng + kFinTile - 1) / kFinTile, nr = (ng + kFinRows - 1) / kFinRows;
+    const int tx = threadIdx.x % kFinTile, ty = threadIdx.x / kFinTile, mx = threadIdx.x % kFinRows, my = threadIdx.x / kFinRows;
     const size_t total = (size_t)ng * ng;
     const global_double2 *part = as_global(P.inplace ? P.chi : P.part), *part_im = as_global(P.part_im);
     global_double2 *chi = as_global(P.chi);
@@ -140,41 +141,26 @@ __global__ __launch_bounds__(256) void k_chi_finalize(const FinProb *__restrict_
         e.x = val.x;
         e.y = val.y;
     };
-    for (int u = blockIdx.x; u < nt * nt; u += gridDim.x) {
-        const int G0 = u / nt * kFinTile, H0 = u % nt * kFinTile;
-        if (G0 > H0) continue;
-        double2 a[4] = {}, b[4] = {};
-        auto sum = [&](const global_double2 *from, double2 (&s)[4]) {
-            for (int p = 0; p < (P.inplace ? 1 : P.ns); ++p)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int G = G0 + ty + 8 * r, H = H0 + tx;
-                    if (G < ng && H < ng) {
-                        const global_double2 &x = from[p * total + (size_t)G * ng + H];
-                        s[r] = make_double2(s[r].x + x.x, s[r].y + x.y);
-                    }
-                }
-        };
-        sum(part, a);
+    for (int u = blockIdx.x; u < nr * nt; u += gridDim.x) {
+        const int G0 = u / nt * kFinRows, H0 = u % nt * kFinTile, G = G0 + ty, H = H0 + tx;
+        if (G0 >= H0 + kFinTile) continue;
+        const size_t at = (size_t)min(G, ng - 1) * ng + min(H, ng - 1);
+        // (outside the matrix an element inside is summed, and dropped)
+        double2 a = make_double2(0.0, 0.0), b = a;
+        const int ns = P.inplace ? 1 : P.ns;
+#pragma unroll 8
+        for (int p = 0; p < ns; ++p) a = make_double2(a.x + part[p * total + at].x, a.y + part[p * total + at].y);
         if (P.part_im) {
-            sum(part_im, b);
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (P.neg_im) b[r] = make_double2(-b[r].x, -b[r].y);
+#pragma unroll 8
+            for (int p = 0; p < ns; ++p) b = make_double2(b.x + part_im[p * total + at].x, b.y + part_im[p * total + at].y);
+            if (P.neg_im) b = make_double2(-b.x, -b.y);
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (G0 + ty + 8 * r == H0 + tx) a[r].y = b[r].y = 0.0;
-            tile[ty + 8 * r][tx] = make_double2(P.pf * (a[r].x + b[r].y), P.pf * (b[r].x - a[r].y));
-        }
+        if (G == H) a.y = b.y = 0.0;
+        tile[ty][tx] = make_double2(P.pf * (a.x + b.y), P.pf * (b.x - a.y));
         __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int G = G0 + ty + 8 * r, H = H0 + tx;
-            if (G <= H && H < ng) store(G, H, make_double2(P.pf * (a[r].x - b[r].y), P.pf * (a[r].y + b[r].x)));
-            const int g = G0 + tx, h = H0 + ty + 8 * r;  // the mirror
-            if (g < h && h < ng) store(h, g, tile[tx][ty + 8 * r]);
-        }
+        if (G <= H && H < ng) store(G, H, make_double2(P.pf * (a.x - b.y), P.pf * (a.y + b.x)));
+        const int g = G0 + mx, h = H0 + my;  // the mirror
+        if (g < h && h < ng) store(h, g, tile[mx][my]);
         __syncthreads();
     }
 }
@@ -366,8 +352,8 @@ int launch_sigma_regroup(const double2 *B, int ng, int ninner, int nouter, doubl
 }
 
 int launch_finalize_batch(const FinProb *probs, int nprob, int maxng, hipStream_t st) {
-    const int nt = (maxng + kFinTile - 1) / kFinTile;
-    const int blocks = std::max(1, std::min(nt * nt, 65536 / std::max(1, nprob) + 1));
+    const int nt = (maxng + kFinTile - 1) / kFinTile, nr = (maxng + kFinRows - 1) / kFinRows;
+    const int blocks = std::max(1, std::min(nr * nt, 65536 / std::max(1, nprob) + 1));
     hipLaunchKernelGGL(k_chi_finalize, dim3(blocks, nprob), dim3(256), 0, st, probs);
     BGW_HIP(hipGetLastError());
     return BGW_OK;

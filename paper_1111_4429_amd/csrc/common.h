@@ -55,7 +55,10 @@ __device__ inline const global_double *as_global(const double *p) { return (cons
 __device__ inline global_double *as_global(double *p) { return (global_double *)p; }
 __device__ inline const global_int *as_global(const int *p) { return (const global_int *)p; }
 
-constexpr int kFinTile = 32;  // tiles in which the finalize kernels write a matrix and its mirror
+// Tiles in which the finalize kernels write a matrix and its mirror, one element per
+// thread: taller ones left a small matrix of many splits on too few CUs (68 vectors,
+// 91520 pairs, real: 1.32 ms a step in 32 x 32).
+constexpr int kFinTile = 32, kFinRows = 8;
 
 // ---------------------------------------------------------------- FFT plans
 // One axis of a 3D transform: length n = product of radices (each 2, 3 or 4),

@@ -172,44 +172,37 @@ __global__ __launch_bounds__(512, 4) void k_syrk_f64(const SyrkProb *__restrict_
 }
 
 // chi[G][H] (+)= pf sum over splits of the raw upper sums, G <= H, in fixed order, and
-// the symmetric mirror.  A block takes 32 x 32 tiles on or above the diagonal: it
+// the symmetric mirror.  A block takes 8 x 32 tiles on or above the diagonal: it
 // sums each element once, in rows, and writes the mirror in rows through LDS (read
 // where it lay, element by element down the columns, it took 0.62 ms at 1500 vectors
 // and six splits; 0.09 now).  In place (ns == 1, part == chi, no accumulation)
 // the same.  grid.y: output matrix.
 __global__ __launch_bounds__(256) void k_syrk_finalize(const SyrkFin *__restrict__ probs) {
-    __shared__ double tile[kFinTile][kFinTile + 1];
+    __shared__ double tile[kFinRows][kFinTile + 1];
     const SyrkFin P = probs[blockIdx.y];
-    const int ng = P.ng, nt = (ng + kFinTile - 1) / kFinTile, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int ng = P.ng, nt = (ng + kFinTile - 1) / kFinTile, nr = (ng + kFinRows - 1) / kFinRows;
+    const int tx = threadIdx.x % kFinTile, ty = threadIdx.x / kFinTile, mx = threadIdx.x % kFinRows, my = threadIdx.x / kFinRows;
     const size_t total = (size_t)ng * ng;
     const global_double *part = as_global(P.part);
     global_double *chi = as_global(P.chi);
-    for (int u = blockIdx.x; u < nt * nt; u += gridDim.x) {
-        const int G0 = u / nt * kFinTile, H0 = u % nt * kFinTile;
-        if (G0 > H0) continue;
-        double a[4] = {};
-        for (int p = 0; p < P.ns; ++p)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int G = G0 + ty + 8 * r, H = H0 + tx;
-                if (G < ng && H < ng) a[r] += part[p * total + (size_t)G * ng + H];
-            }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tile[ty + 8 * r][tx] = a[r] = P.pf * a[r];
+    for (int u = blockIdx.x; u < nr * nt; u += gridDim.x) {
+        const int G0 = u / nt * kFinRows, H0 = u % nt * kFinTile, G = G0 + ty, H = H0 + tx;
+        if (G0 >= H0 + kFinTile) continue;
+        const size_t at = (size_t)min(G, ng - 1) * ng + min(H, ng - 1);
+        // (outside the matrix an element inside is summed, and dropped)
+        double a = 0.0;
+#pragma unroll 8
+        for (int p = 0; p < P.ns; ++p) a += part[p * total + at];
+        tile[ty][tx] = a = P.pf * a;
         __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int G = G0 + ty + 8 * r, H = H0 + tx;
-            if (G <= H && H < ng) {
-                global_double &e = chi[(size_t)G * ng + H];
-                e = P.accumulate ? e + a[r] : a[r];
-            }
-            const int g = G0 + tx, h = H0 + ty + 8 * r;  // the mirror
-            if (g < h && h < ng) {
-                global_double &e = chi[(size_t)h * ng + g];
-                const double x = tile[tx][ty + 8 * r];
-                e = P.accumulate ? e + x : x;
-            }
+        if (G <= H && H < ng) {
+            global_double &e = chi[(size_t)G * ng + H];
+            e = P.accumulate ? e + a : a;
+        }
+        const int g = G0 + mx, h = H0 + my;  // the mirror
+        if (g < h && h < ng) {
+            global_double &e = chi[(size_t)h * ng + g];
+            e = P.accumulate ? e + tile[mx][my] : tile[mx][my];
         }
         __syncthreads();
     }
@@ -257,8 +250,8 @@ int syrk_blocks_per_cu() {
 }
 
 int launch_syrk_finalize(const SyrkFin *probs, int nprob, int maxng, hipStream_t st) {
-    const int nt = (maxng + kFinTile - 1) / kFinTile;
-    const int blocks = std::max(1, std::min(nt * nt, 65536 / std::max(1, nprob) + 1));
+    const int nt = (maxng + kFinTile - 1) / kFinTile, nr = (maxng + kFinRows - 1) / kFinRows;
+    const int blocks = std::max(1, std::min(nr * nt, 65536 / std::max(1, nprob) + 1));
     hipLaunchKernelGGL(k_syrk_finalize, dim3(blocks, nprob), dim3(256), 0, st, probs);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
