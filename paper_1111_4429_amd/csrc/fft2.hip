@@ -852,7 +852,7 @@ namespace {
 constexpr long long kLineWgs = 2048;
 int lines_xblk(int n1, int G, long long per_block, int rounds = 4, long long wgs = kLineWgs) {
     int r = std::max(1, std::min((n1 + G - 1) / G, rounds));
-    while (r > 1 && per_block * ((n1 + r * G - 1) / (r * G)) < wgs) --r;
+    while (r > 1 && per_block * ((n1 + r * G - 1) / (r * G)) < wgs) r = (r + 1) / 2;  // (equal shares)
     return r * G;
 }
 
