@@ -845,11 +845,11 @@ __global__ __launch_bounds__(64) void k_band_yz(const double2 *__restrict__ W, i
 namespace {
 // x-planes per workgroup of a pass: up to `rounds` rounds of G (fewer workgroups to
 // start, longer streams) while that leaves `wgs` workgroups, for the lane-per-line
-// passes the eight per CU that their registers allow; else fewer rounds, and in
+// passes the four per CU that 32-point lines leave room for; else fewer rounds, and in
 // pass A then fewer valence bands per workgroup.  128 conduction times 64 valence
-// bands on 32^3: 512 workgroups 1531 us, 2048 941 us; 16 times 4 on 16^3: 16
+// bands on 32^3: 512 workgroups 1531 us, 1024 0.92 ms; 16 times 4 on 16^3: 16
 // workgroups 34 us, 64 9.7 us.
-constexpr long long kLineWgs = 2048;
+constexpr long long kLineWgs = 1024;
 int lines_xblk(int n1, int G, long long per_block, int rounds = 4, long long wgs = kLineWgs) {
     int r = std::max(1, std::min((n1 + G - 1) / G, rounds));
     while (r > 1 && per_block * ((n1 + r * G - 1) / (r * G)) < wgs) r = (r + 1) / 2;  // (equal shares)
