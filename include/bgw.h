@@ -297,7 +297,7 @@ int bgw_realify_workspace(bgw_handle_t h, int nk, int nb, int ngw, const double 
  * transposed into the workspace (G becomes the contraction index, the G0
  * row zeroed) and the chi-sum kernels run with the weights v, FP64 or split
  * form as in bgw_chi0.  Kx is Hermitian positive semidefinite for v > 0.
- * The split form scales its digits per run of 384 consecutive G vectors, so a
+ * The split form scales its digits per run of 96 consecutive G vectors, so a
  * term orders of magnitude above its neighbours (v(q0+0) ~ 1/q0^2 at small q
  * with head = -1) costs digits of the whole run: leave G = 0 out through
  * `head`, or use FP64, when v has such a term.

@@ -414,7 +414,8 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
         size_t hw = 0, ew_all = 0;
         for (int iq = 0; iq < d->nq; ++iq) {
             if (d->q[iq].head >= 0) hw = std::max(hw, sizeof(double2) * (size_t)kHeadSplits * vq * d->q[iq].ng);
-            ew_all += al256(split_ea_bytes(vq, split_chunks(q_pairs(d->q[iq])), d->q[iq].ng));
+            const long long K = q_pairs(d->q[iq]);
+            ew_all += al256(split_ea_bytes(vq, split_steps(K, 0, split_chunks(K)), d->q[iq].ng));
         }
         // slice budget: what the device holds next to everything else of the call
         const size_t other = off + al256(hw) + ew_all + ((size_t)2 << 30);
@@ -449,8 +450,8 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
             for (auto &r : ranges) {
                 const int iq = r.first;
                 const long long nchr = r.second.second - r.second.first;
-                const size_t b = al256(
-                    split_slice_bytes(nchr, split_steps(q_pairs(d->q[iq]), r.second.first, nchr), d->q[iq].ng));
+                const long long nst = split_steps(q_pairs(d->q[iq]), r.second.first, nchr);
+                const size_t b = al256(split_slice_bytes(nchr, nst, d->q[iq].ng));
                 const bool whole = r.second.first == 0 && r.second.second == split_chunks(q_pairs(d->q[iq]));
                 if (!cur.qs.empty() && (!whole || cur_bytes + b > budget)) close();
                 SplitQ e;
@@ -462,7 +463,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
                 cur.sb_off.push_back(cur_bytes);
                 cur.ew_off.push_back(cur_ew);
                 cur_bytes += b;
-                cur_ew += al256(split_ea_bytes(vq, nchr, d->q[iq].ng));
+                cur_ew += al256(split_ea_bytes(vq, nst, d->q[iq].ng));
                 if (!whole) close();
                 if (!whole && P.qpart_off[iq] == (size_t)-1) {  // several launches: sums through partials
                     P.qpart_off[iq] = off;
@@ -483,6 +484,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
                 e.K = q_pairs(q);
                 e.ng = q.ng;
                 e.gpad = split_gpad(q.ng);
+                e.apad = split_apad(q.ng);
                 e.nvec = vq;
                 e.ntiles = (int)P.tiles[iq].size();
                 // every split non-empty; the first range of a q holds enough steps for q_ns
@@ -570,7 +572,7 @@ void bind_plan(const bgw_chi_desc *d, ChiPlan &P, char *ws, char *tab) {
             e.SB = (const unsigned char *)(ws + P.off_slices + L.sb_off[i]);
             e.EC = (const int *)((const char *)e.SB + split_slices_only_bytes(e.nst, e.ng));
             e.EB = (const short *)((const char *)e.EC + split_ec_bytes(e.nst, e.ng));
-            e.EA = (const short *)(ws + P.off_ew + L.ew_off[i]);
+            e.EA = (const signed char *)(ws + P.off_ew + L.ew_off[i]);
             e.out = P.qpart_off[iq] == (size_t)-1 ? (double2 *)q.chi : (double2 *)(ws + P.qpart_off[iq]);
             e.vstride = (long long)(P.qpart_off[iq] == (size_t)-1 ? 1 : P.q_ns[iq]) * q.ng * q.ng;
             e.tiles = (const unsigned *)(tab + P.tiles_off[iq]);
@@ -627,7 +629,7 @@ int enqueue(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, char *ws, char *t
             for (size_t i = 0; i < L.qs.size(); ++i) {
                 const SplitQ &e = L.qs[i];
                 BGW_TRY(launch_split_slices(e.M, e.K, e.ng, e.chunk0, e.nch, e.nst, (unsigned char *)e.SB, (short *)e.EB, e.w,
-                                            e.wstride, e.nvec, (short *)e.EA, (int *)e.EC, st));
+                                            e.wstride, e.nvec, (signed char *)e.EA, (int *)e.EC, st));
             }
         }
         {

@@ -115,7 +115,7 @@ struct SplitQ {
     const double *w;           // weight vector v at w + v * wstride, [K] each
     const unsigned char *SB;   // digit slices of M for the launch's chunks: [nch][12][5][gpad][64] bytes
     const int *EC;             // running sums of their Re digits: [nch][12][5][gpad]
-    const short *EB;           // their chunk-column exponents: [nch][gpad]
+    const short *EB;           // their exponents: [nch][gpad][4], one per run of 96 pairs
     double2 *out;              // raw upper-tile sums of (vector v, K split s): out + v * vstride + s * ng * ng
     const unsigned *tiles;     // upper tiles (64-row x 96-column) in walk order: I | J << 16
     long long K, wstride, vstride;
@@ -125,8 +125,8 @@ struct SplitQ {
     int nst;                   // its k-steps (32 pairs) that hold pairs < K
     int ns;                    // K splits: with u = ceil(nst / 2), split s takes the steps 2 [s u / ns, (s + 1) u / ns)
     int add;                   // 1: add to the raw sums already in out (later chunk ranges)
-    int pad;
-    const short *EA;           // [nvec][nch][gpad] chunk-column exponents of the weighted side
+    int apad;
+    const signed char *EA;     // [nvec][runs][apad] exponents of the weighted side, less EB's
 };
 
 // Upper-triangle tile number u -> (ti, tj) in grouped order: bands of four

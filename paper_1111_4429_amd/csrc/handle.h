@@ -129,12 +129,13 @@ size_t split_slice_bytes(long long nch, long long nst, int ng);  // slices, digi
 size_t split_slices_only_bytes(long long nst, int ng);  // the slices alone (the digit sums follow them)
 size_t split_ec_bytes(long long nst, int ng);   // the digit sums (the exponents follow them)
 size_t split_chunk_bytes(int ng);               // split_slice_bytes of one full chunk
-size_t split_ea_bytes(long long nvec, long long nch, int ng);  // weighted-side exponents
+int split_apad(int ng);                         // columns of the weighted-side exponents
+size_t split_ea_bytes(long long nvec, long long nst, int ng);  // weighted-side exponents of nst k-steps
 void split_tiles(int ng, std::vector<unsigned> &out);  // upper 64 x 96 tiles in walk order
 long long split_wide_tiles(int ng);             // upper tiles if they were 64 x 128
 int split_grid();                               // blocks of the persistent split launch
 int launch_split_slices(const double2 *M, long long K, int ng, long long c0, int nch, int nst, unsigned char *S,
-                        short *E, const double *w, long long wstride, int nvec, short *EA, int *EC, hipStream_t);
+                        short *E, const double *w, long long wstride, int nvec, signed char *EA, int *EC, hipStream_t);
 int launch_chi_split(const SplitQ *qs, int nq, long long nitems, hipStream_t);
 int launch_headwing(const double2 *M, long long K, int ng, int head, const double *w, long long wstride, int nvec,
                     int nsplit, double2 *hw, hipStream_t);

@@ -2,11 +2,15 @@
 // M^H diag(w) M, see chi.hip) computed from 8-bit digit slices on INT8 MFMA
 // with exact INT32 accumulation, recombined in FP64.
 //
-// Digits.  The pairs are cut into chunks of 384 (twelve MFMA k-steps of 32).
-// Within a chunk every column G of X gets a power-of-two scale 2^eB (above the
-// chunk-column max of |Re M|, |Im M|), and every column of X_w, for each
-// weight vector, the scale 2^eA above the chunk-column max of |w_t Re M|,
-// |w_t Im M| (both found by k_split_slice in its pass over M).  Each scaled
+// Digits.  The pairs are cut into chunks of 384 (twelve MFMA k-steps of 32),
+// each of four runs of 96.  Within a run every column G of X has a power-of-two
+// scale 2^eB (above the column's max of |Re M|, |Im M|), and every column of
+// X_w, for each weight vector, a scale 2^eA above the max of |w_t Re M|, |w_t
+// Im M| (both found by k_split_slice in its pass over M).  A run whose max lies
+// at most a factor 2 (eB) or 8 (eA) below the chunk's shares the chunk's scale, a
+// lower one has its own (run_exp): the INT32 sums of a tile then run over the
+// whole chunk where the pairs are alike, and end at the runs in which some
+// column of the tile changes its scale.  Each scaled
 // value is rounded once to a 40-bit integer N = rint(x 2^(39-e)) and written as
 // five signed base-256 digits, N = sum_i d_i 256^(4-i), -128 <= d_i <= 127.
 // One FMA with the constant 1.5 2^52 + 0x8080808080 makes all five: the low 40
@@ -27,9 +31,13 @@
 // p; every sum is exact (|sum| <= 5 2^14 768 < 2^26).  Fifteen INT8 MFMA
 // products per (Re, Im); at each chunk end the five sums are combined in FP64
 // with the chunk scales and added to FP64 accumulators.  Dropped: products of
-// weight 2^-40 of the leading one and below, and the rounding of N (2^-40 of
-// the chunk-column max).  A column with a value that is not finite gets the
-// exponent kNotFinite, which makes its sums NaN.
+// weight 2^-40 of the leading one and below, and the rounding of N: in all at
+// most 74 2^-40 of a run's largest product, for the shared scales (8 + 2 units of
+// rounding, 4 digit products of weight 2^-40 a factor 8 x 2 up).  Four 9-bit digits
+// with a scale per 96 pairs, as BF16 products need them, leave 80.  One scale per
+// chunk whatever its runs hold was up to the ratio of the runs worse.  A column
+// with a value that is not finite gets the exponent kNotFinite, which makes its
+// sums NaN.
 //
 // Why INT8: the card's INT8 MFMA has twice the BF16 rate, so fifteen exact
 // 8-bit products cost 3/4 of the ten BF16 products that four 9-bit digits
@@ -52,7 +60,10 @@ typedef int int6_t __attribute__((ext_vector_type(6)));
 namespace {
 constexpr int KSP = 32;       // pairs per MFMA k-step (16x16x64: 64 real rows)
 constexpr int NKS = 12;       // k-steps per chunk
-constexpr int SKP = KSP * NKS; // pairs per chunk (one set of exponents)
+constexpr int SKP = KSP * NKS; // pairs per chunk
+constexpr int RKS = 3;        // k-steps per run (96 pairs, one exponent per column)
+constexpr int NRUN = NKS / RKS;
+constexpr int SLACK_A = 3, SLACK_B = 1;  // powers of two by which a run may lie below the scale it shares
 constexpr int UKS = 2;        // K splits are cut at multiples of this many k-steps
 constexpr int KSB = 2 * KSP;  // bytes of one column's digits of one slice and k-step
 constexpr int NSL = 5;        // digits (stored slices of the unweighted side, INT32 product groups)
@@ -61,7 +72,9 @@ constexpr int TR = 64;        // output tile rows: weighted side, sliced in regi
 constexpr int TC = 32 * NCB;  // output tile columns: unweighted side, digit slices through LDS
 constexpr int XT = 512;       // GEMM block: 8 waves (two per SIMD), 4 x 2 over the tile
 constexpr int kMinExp = -500; // chunk exponents are clamped here (values below 2^-539 count as zero)
-constexpr int kNotFinite = 0x7fff;  // exponent of a chunk column with a value that is not finite
+constexpr int kNotFinite = 3071;    // exponent of a chunk column with a value that is not finite
+constexpr int kZeroRun = -0x7fff;   // raw exponent of a run without a value
+constexpr int kNotFiniteA = 127;    // the same in the weighted side's exponents, bytes relative to eB
 constexpr double kFixBias = 6755399441055744.0 + 551911719040.0;  // 1.5 2^52 + 0x8080808080
 constexpr unsigned kToggle = 0x80808080u;
 
@@ -74,6 +87,37 @@ __device__ inline int chunk_exp(double mx) {
     int e = 0;
     if (mx > 0.0) (void)frexp(mx * 1.005, &e);
     return max(e, kMinExp);
+}
+
+// Exponent of run r from the chunk's raw ones: the chunk's largest where run r lies
+// at most `slack` below it, else that less a multiple of slack + 1.  A run without a
+// value takes a neighbour's (it would end the sums for nothing).
+__device__ inline int run_exp(const int (&e)[NRUN], int r, int slack) {
+    int top = kZeroRun, x = kZeroRun;
+#pragma unroll
+    for (int s = 0; s < NRUN; ++s) {
+        top = max(top, e[s]);
+        if (e[s] != kZeroRun && (s <= r || x == kZeroRun)) x = e[s];
+    }
+    if (top == kNotFinite || top == kZeroRun) return top;
+    return top - (top - x) / (slack + 1) * (slack + 1);
+}
+
+// A stored eB: the exponent in 12 bits, and whether the column's scale differs from that of
+// the run before: its own, or with any weight vector.  (The sums of all vectors end at the
+// same runs, needed or not: blocks that read the same rows of M for several vectors
+// otherwise drift apart and miss L2: six real frequencies of two q with 1500 and 731
+// vectors, whose weights differ by up to 2^11 within most chunks, 34.6 ms against 30.0.)
+constexpr int kExpBits = 0xfff, kExpBias = 1024, kOwnChange = 0x1000, kAnyChange = 0x2000;
+__device__ __forceinline__ int exp_of(int stored) { return (stored & kExpBits) - kExpBias; }
+
+// run_exp of run r = lane mod 4 from the four lanes' maxima
+__device__ inline int quad_run_exp(double mx, int slack) {
+    const int raw = mx == 0.0 ? kZeroRun : chunk_exp(mx), lane = threadIdx.x & 63;
+    int e[NRUN];
+#pragma unroll
+    for (int s = 0; s < NRUN; ++s) e[s] = __shfl(raw, (lane & ~(NRUN - 1)) + s, 64);
+    return run_exp(e, lane & (NRUN - 1), slack);
 }
 
 // The digits of N = rint(x s) plus 128 in the low 40 bits: lo holds digits 4
@@ -107,34 +151,43 @@ __device__ __forceinline__ double abs_max(double2 z) {
 }  // namespace
 
 // Digit slices of the unweighted side for chunks [c0, c0 + nchunk) of one q,
-// and the chunk-column exponents of the weighted side of every weight vector.
+// and the exponents of the weighted side of every weight vector.
 // Block = one chunk x 32 columns, 768 threads.  Thread t owns column G = 32
 // blockIdx.x + (t/4) % 32 and, in each of the k-steps 2 (t/128) and
 // 2 (t/128) + 1, the eight pairs 8 (t%4) .. +7; with this assignment every
 // 16-byte store instruction of a wave writes 1 KB of contiguous slice memory.
 // S: [k-step][NSL][gpad][KSB] bytes, each group of 16 holding eight pairs as
-// (Re t0..t7, Im t0..t7); E: [nchunk][gpad]; EA: [nvec][nchunk][gpad]
-// (chunk_exp of the chunk-column max of |Re M|, |Im M| and of |w_v(t) Re M|,
-// |w_v(t) Im M|).  EC: [k-step][NSL][gpad], entry p the sum of the Re digits 0
+// (Re t0..t7, Im t0..t7); E: [nchunk][gpad][NRUN], eB of the chunk's runs (exp_of); EA:
+// [nvec][runs][apad], eA - eB (within a byte: the size of the weights; below 2^-128 a
+// weight keeps fewer digits, above 2^126 it counts as not finite).
+// EC: [k-step][NSL][gpad], entry p the sum of the Re digits 0
 // .. p of the column over the chunk's k-steps up to this one.  Pairs >= K are
 // zero; only the first nst k-steps, those that hold pairs < K, are stored.
 constexpr int SLICE_T = 32 * 4 * (NKS / 2);  // 768
 __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restrict__ M, long long K, int ng, int gpad,
-                                                         long long c0, int nchunk, int nst, unsigned char *__restrict__ S,
+                                                         long long c0, int nst, unsigned char *__restrict__ S,
                                                          short *__restrict__ E, const double *__restrict__ w,
-                                                         long long wstride, int nvec, short *__restrict__ EA,
-                                                         int *__restrict__ EC) {
-    constexpr int NP = 4 * (NKS / 2);  // partial maxima per column
-    __shared__ double red[NP][32];
+                                                         long long wstride, int nvec, signed char *__restrict__ EA,
+                                                         int apad, int *__restrict__ EC) {
+    constexpr int NP = 4 * RKS;        // partial maxima per column and run
+    __shared__ double red[4 * NKS][33];
+    __shared__ int ex[NRUN][32];
     __shared__ int dsum[NKS][NSL][32];
     const int q = threadIdx.x & 3, cl = (threadIdx.x >> 2) & 31, kh = threadIdx.x >> 7;
     const int G = blockIdx.x * 32 + cl;
     const int chunk = blockIdx.y;
     const long long tb = (c0 + chunk) * SKP + 2 * kh * KSP + 8 * q;  // k-step i, pair j: tb + KSP i + j
     const bool col = G < ng;
+    // the first 128 threads reduce: thread t run t % 4 of column t / 4 (its cl)
+    const bool reduces = threadIdx.x < 32 * NRUN;
+    auto run_max = [&]() {
+        double mx = 0.0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) mx = fmax(mx, red[NP * q + k][cl]);
+        return mx;
+    };
     double2 m[2][8];  // [k-step i][pair j]
     double mr[2][8];
-    double mx = 0.0;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -143,22 +196,32 @@ __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restri
             m[i][j] = (t < K && col) ? M[t * ng + G] : make_double2(0.0, 0.0);
         }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
+        double mx = 0.0;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             mr[i][j] = abs_max(m[i][j]);
             mx = fmax(mx, mr[i][j]);
         }
-    red[4 * kh + q][cl] = mx;
+        red[4 * (2 * kh + i) + q][cl] = mx;
+    }
     __syncthreads();
-    mx = 0.0;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) mx = fmax(mx, red[k][cl]);
-    const int e = chunk_exp(mx);
-    if (q == 0 && kh == 0) E[(size_t)chunk * gpad + G] = (short)e;
-    const double up = e == kNotFinite ? 0.0 : pow2(39 - e);
+    int eb = 0, own = 0, any = 0;  // of the reducing threads' runs: eB, and whether a scale changes there
+    auto changes = [&](int e) {
+        const int before = __shfl_up(e, 1, 64);
+        return q > 0 && before != e;
+    };
+    if (reduces) {
+        eb = quad_run_exp(run_max(), SLACK_B);
+        if (eb == kZeroRun) eb = 0;
+        own = changes(eb);
+        ex[q][cl] = eb;
+    }
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
+        const int e = ex[(2 * kh + i) / RKS][cl];
+        const double up = e == kNotFinite ? 0.0 : pow2(39 - e);
         unsigned d[4][NSL];  // [Re t0..3, Re t4..7, Im t0..3, Im t4..7]
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -193,11 +256,13 @@ __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restri
         }
     }
     // weighted side: |w| max(|Re M|, |Im M|) bounds the products the GEMM rounds
+    const int nrun = (nst + RKS - 1) / RKS, run = chunk * NRUN + q;
     for (int v = 0; v < nvec; ++v) {
         const double *wv = w + (size_t)v * wstride;
-        double mw = 0.0;
+        __syncthreads();  // the previous reduction has been read
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i) {
+            double mw = 0.0;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const long long t = tb + KSP * i + j;
@@ -206,16 +271,20 @@ __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restri
                     mw = x <= 1.7e308 ? fmax(mw, x) : INFINITY;
                 }
             }
-        __syncthreads();  // the previous vector's reduction has been read
-        red[4 * kh + q][cl] = mw;
+            red[4 * (2 * kh + i) + q][cl] = mw;
+        }
         __syncthreads();
-        if (q == 0 && kh == 0) {
-            mw = 0.0;
-#pragma unroll
-            for (int k = 0; k < NP; ++k) mw = fmax(mw, red[k][cl]);
-            EA[((size_t)v * nchunk + chunk) * gpad + G] = (short)chunk_exp(mw);
+        if (reduces) {
+            const int e = quad_run_exp(run_max(), SLACK_A);
+            int rel = e == kZeroRun ? 0 : max(e - eb, -128);
+            if (e == kNotFinite || rel >= kNotFiniteA) rel = kNotFiniteA;
+            any |= changes(eb + rel);
+            if (run < nrun && G < apad) EA[((size_t)v * nrun + run) * apad + G] = (signed char)rel;
         }
     }
+    if (reduces)
+        E[((size_t)chunk * gpad + G) * NRUN + q] =
+            (short)((eb + kExpBias) | (own ? kOwnChange : 0) | (own || any ? kAnyChange : 0));
 }
 
 namespace {
@@ -233,16 +302,19 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // slices, [slice][96 rows][64 B] with the four 16-B segments of row r stored
 // in the order seg ^ ((r >> 1) & 3), so that the eight rows one 16-B read
 // phase touches fall in distinct bank groups; the step's 32 weights.
-// Besides the two stages, two chunk buffers hold a chunk's column exponents
-// (int16, bytes 0..191), 64 row exponents of the weighted side (int16, bytes
-// 256..383) and the digit sums at the item's last k-step in it ([5][96] int32
-// from byte 512 on): chunk c in buffer c % 2, staged with the first step that
-// needs it and read when the chunk starts and when it ends.
+// Besides the two stages, two chunk buffers hold eB of a chunk's 96 columns (int16,
+// [column][run]), eA - eB of its 64 rows (int8, [run][row]), eB of its rows and the
+// digit sums at the end of each run ([run][5][96] int32; of the last one at the
+// item's last k-step in it): chunk c in buffer c % 2, staged with the first
+// step that needs it and read where the sums start and end.  Every load to LDS
+// is one of a whole wave, 1 KB.
 constexpr int A_LDS = KSP * TR * 16;          // 32 KB
 constexpr int B_SLICE_LDS = TC * KSB;         // 6 KB
 constexpr int W_OFF = A_LDS + NSL * B_SLICE_LDS;
-constexpr int STG = W_OFF + 256;              // 62.25 KB
-constexpr int EC_OFF = 512, E_LDS = EC_OFF + NSL * TC * 4;
+constexpr int STG = W_OFF + 1024;             // 63 KB
+constexpr int EA_OFF = TC * NRUN * 2, EBR_OFF = EA_OFF + TR * NRUN, EC_OFF = EBR_OFF + 1024;
+constexpr int EC_RUN = NSL * TC * 4, EC_PIECES = (NRUN * EC_RUN + 1023) / 1024, E_LDS = EC_OFF + EC_PIECES * 1024;
+static_assert(EBR_OFF == 1024 && TR * NRUN * 2 <= 1024, "eB of the columns and eA - eB of the rows in one load");
 constexpr int NWAVE = XT / 64;
 constexpr int PA = KSP / NWAVE;               // 1-KB pieces of the A part per wave: 4
 constexpr int NB_PIECES = NSL * B_SLICE_LDS / 1024;          // of the B part, all waves: 30
@@ -270,17 +342,17 @@ struct StageSrc {
     unsigned b0;             // the tile's first column in it
     int b_off;               // lane L of a piece: row L/4, source segment (L%4) ^ ((L/8) & 3)
     const double *w;         // weights of this vector at the launch's first pair
-    const short *eb;         // EB: chunk-column exponents of the slices, [nch][gpad]
-    const short *ea;         // EA of this vector: chunk-column exponents of the weighted side, [nch][gpad]
+    const short *eb;         // EB: exponents of the slices, [nch][gpad][NRUN]
+    const signed char *ea;   // EA of this vector: of the weighted side, less EB's, [nrun][apad]
     const int *ec;           // EC at the tile's first column
-    int gpad, G0, H0, s1;    // s1: the item's last k-step + 1
+    int gpad, apad, nrun, G0, H0, s1;  // s1: the item's last k-step + 1
 };
 
 // One k-step x into one stage.  A piece i of wave w is pair row 4w + i of the
 // k-step (past K the last pair again: it meets zero digits of the other side);
 // B piece p = w + 8 i is slice p / 6, rows 16 (p % 6) .. +16.  Wave 7 loads the
-// step's weights (lanes 0..15, two each; the vectors are padded by 128 entries)
-// and wave 6 the exponents of the step's chunk when they are new.
+// step's weights (two per lane, four times over; the vectors are padded by 128
+// entries) and wave 6 the exponents of the step's chunk when they are new.
 __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, unsigned char *__restrict__ ebuf,
                                             const StageSrc &S, int x, bool first, int wave, int lane) {
     const long long t0 = (long long)x * KSP;
@@ -303,25 +375,28 @@ __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, u
                 (int)(S.b0 + (p / (TC / 16)) * S.b_slice + (p % (TC / 16)) * 1024), 0, 0);
     }
     if (wave == NWAVE - 1) {
-        if (lane < 16)
-            __builtin_amdgcn_global_load_lds((const void *)(S.w + t0 + 2 * lane), (lds_void_t *)(stage + W_OFF), 16, 0,
-                                             0);
+        __builtin_amdgcn_global_load_lds((const void *)(S.w + t0 + 2 * (lane & 15)), (lds_void_t *)(stage + W_OFF), 16, 0,
+                                         0);
     } else if (wave == NWAVE - 2 && (first || x % NKS == 0)) {
-        const long long ch = x / NKS;
-        // 8 exponents per lane; rows past gpad (whose sums are not stored) repeat the last ones
-        if (lane < TC / 8)
-            __builtin_amdgcn_global_load_lds((const void *)(S.eb + ch * S.gpad + S.H0 + 8 * lane), (lds_void_t *)ebuf,
-                                             16, 0, 0);
-        if (lane < TR / 8)
-            __builtin_amdgcn_global_load_lds(
-                (const void *)(S.ea + ch * S.gpad + min(S.G0 + 8 * lane, S.gpad - 8)), (lds_void_t *)(ebuf + 256), 16,
-                0, 0);
-        const long long last = min(S.s1, ((int)ch + 1) * NKS) - 1;
-        if (lane < TC / 4) {
+        const int ch = x / NKS;
+        int l = lane;
+        asm volatile("" : "+v"(l));  // the addresses are made here: kept over the steps they cost registers
+        // eB of two columns per lane, eA - eB of 16 rows per lane (a run past the last repeats it; columns and
+        // rows past the matrix, whose sums are not stored, others)
+        const short *eb = S.eb + (size_t)ch * S.gpad * NRUN;
+        const signed char *ea = S.ea + (size_t)min(S.nrun - 1, ch * NRUN + l % 16 / (TR / 16)) * S.apad +
+                                min(S.G0 + l % (TR / 16) * 16, S.apad - 16);
+        const void *e = l < TC / 2 ? (const void *)(eb + min(S.H0 + 2 * l, S.gpad - 2) * NRUN) : (const void *)ea;
+        __builtin_amdgcn_global_load_lds(e, (lds_void_t *)ebuf, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((const void *)(eb + min(S.G0 + 2 * (l % (TR / 2)), S.gpad - 2) * NRUN),
+                                         (lds_void_t *)(ebuf + EBR_OFF), 16, 0, 0);
 #pragma unroll
-            for (int p = 0; p < NSL; ++p)
-                __builtin_amdgcn_global_load_lds((const void *)(S.ec + (last * NSL + p) * S.gpad + 4 * lane),
-                                                 (lds_void_t *)(ebuf + EC_OFF + p * TC * 4), 16, 0, 0);
+        for (int h = 0; h < EC_PIECES; ++h) {
+            const int i = min(64 * h + l, NRUN * EC_RUN / 16 - 1);  // 16 bytes: four columns of an entry of a run
+            const int last = min(S.s1, ch * NKS + RKS * (i / (EC_RUN / 16) + 1)) - 1, j = i % (EC_RUN / 16);
+            __builtin_amdgcn_global_load_lds(
+                (const void *)(S.ec + ((size_t)last * NSL + j / (TC / 4)) * S.gpad + j % (TC / 4) * 4),
+                (lds_void_t *)(ebuf + EC_OFF + h * 1024), 16, 0, 0);
         }
     }
 }
@@ -380,22 +455,43 @@ __device__ __forceinline__ void split_mfma(const SplitFrags &A, const uint4 (&bf
 // 2^(e - 7), NaN for a column with a value that is not finite
 __device__ __forceinline__ double exp_scale(int e) { return e == kNotFinite ? NAN : pow2(e - 7); }
 
-// Chunk end: the five INT32 groups combined in FP64 with the chunk scales
-// 2^(eA + eB - 14) into the FP64 accumulators.  D layout of 16x16x64: lane
+// eB of a column, eA of a row and the digit sums at the end of run r, from a chunk's buffer
+__device__ __forceinline__ int col_exp(const unsigned char *E, int c, int r) {
+    return exp_of(reinterpret_cast<const short *>(E)[NRUN * c + r]);
+}
+__device__ __forceinline__ int row_exp(const unsigned char *E, int g, int r) {
+    const int b = exp_of(reinterpret_cast<const short *>(E + EBR_OFF)[NRUN * g + r]);
+    const int a = reinterpret_cast<const signed char *>(E + EA_OFF)[TR * r + g];
+    return a == kNotFiniteA ? kNotFinite : a + b;
+}
+__device__ __forceinline__ const int *digit_sums(const unsigned char *E, int r) {
+    return reinterpret_cast<const int *>(E + EC_OFF + r * EC_RUN);
+}
+
+// Bit r: some column or row of the tile changes its scale at run r.
+__device__ __forceinline__ int scale_changes(const unsigned char *E, int lane) {
+    const uint2 *cols = reinterpret_cast<const uint2 *>(E), *rows = reinterpret_cast<const uint2 *>(E + EBR_OFF);
+    const uint2 c0 = cols[lane], c1 = cols[64 + lane % (TC - 64)], rb = rows[lane];
+    constexpr unsigned own = kOwnChange * 0x10001u, any = kAnyChange * 0x10001u;
+    const unsigned r01 = ((c0.x | c1.x) & own) | (rb.x & any), r23 = ((c0.y | c1.y) & own) | (rb.y & any);
+    return (__ballot(r01 >> 16 != 0) ? 2 : 0) | (__ballot((r23 & 0xffff) != 0) ? 4 : 0) |
+           (__ballot(r23 >> 16 != 0) ? 8 : 0);
+}
+
+// End of the sums at a run's end: the five INT32 groups combined in FP64 with the
+// scales 2^(eA + eB - 14) into the FP64 accumulators.  D layout of 16x16x64: lane
 // l, register r -> row 4 (l/16) + r, col l % 16.  E: the chunk's buffer.
-__device__ __forceinline__ void split_flush(SplitAcc &acc, const unsigned char *E, int wave, int li, int lq) {
-    const short *Eb = reinterpret_cast<const short *>(E);
-    const short *Ea = reinterpret_cast<const short *>(E + 256);
+__device__ __forceinline__ void split_flush(SplitAcc &acc, const unsigned char *E, int run, int wave, int li, int lq) {
+    const int *ec = digit_sums(E, run);
     double pa[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) pa[r] = exp_scale(Ea[16 * (wave >> 1) + 4 * lq + r]);
+    for (int r = 0; r < 4; ++r) pa[r] = exp_scale(row_exp(E, 16 * (wave >> 1) + 4 * lq + r, run));
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
-        const double pb = exp_scale(Eb[16 * NCB * (wave & 1) + 16 * cb + li]);
+        const double pb = exp_scale(col_exp(E, 16 * NCB * (wave & 1) + 16 * cb + li, run));
         int corr[NSL];
 #pragma unroll
-        for (int p = 0; p < NSL; ++p)
-            corr[p] = reinterpret_cast<const int *>(E + EC_OFF)[p * TC + 16 * NCB * (wave & 1) + 16 * cb + li];
+        for (int p = 0; p < NSL; ++p) corr[p] = ec[p * TC + 16 * NCB * (wave & 1) + 16 * cb + li];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             double v[2];
@@ -470,11 +566,13 @@ __device__ __forceinline__ void split_step(const unsigned char *__restrict__ cur
 // the 32 weights into LDS with direct global->LDS loads, one step ahead
 // through two stages; each wave slices its 16 rows of w_t M_t(G) into
 // digits in registers and issues 90 MFMAs.
-// What bounds it (Ng = 4000, K = 40 960, four frequencies: 68.4 ms, 2.4 POPS;
+// What bounds it (Ng = 4000, K = 40 960, four frequencies: 69.4 ms, 2.3 POPS;
 // the BF16 form took 108.4): the MFMAs alone take 42.6 ms, at the 3.7 POPS
 // that the card holds on such data (4.7 on zeros: the clock falls with the
 // power); reading the fragments from LDS adds 7 ms, the barrier 3, the loads
-// into LDS 10 when they hit L2 and 6 more as they miss.
+// into LDS 10 when they hit L2 and 6 more as they miss.  Ending the sums at
+// every run, four times a chunk, would make it 84 ms; the real-axis sums above,
+// which do so at most runs, take 27.9 ms, and 23.4 with sums over whole chunks.
 // out (+)= raw sums (no prefactor) of every element of the tile inside ng x ng.
 __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ qs, int nq, long long i0,
                                                      long long i1) {
@@ -518,7 +616,9 @@ __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ 
         S.b_off = (lane >> 2) * KSB + 16 * ((lane & 3) ^ ((lane >> 3) & 3));
         S.w = Q.w + (size_t)v * Q.wstride + (long long)Q.chunk0 * SKP;
         S.eb = Q.EB;
-        S.ea = Q.EA + (size_t)v * Q.nch * gpad;
+        S.nrun = (Q.nst + RKS - 1) / RKS;
+        S.apad = Q.apad;
+        S.ea = Q.EA + (size_t)v * S.nrun * Q.apad;
         S.gpad = gpad;
         S.G0 = G0;
         S.H0 = H0;
@@ -541,13 +641,19 @@ __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ 
         BGW_WAIT_VM(0);
         stage_barrier();
 
-        for (int xc = s0; xc < s1;) {  // one chunk, or the item's part of it
-            const int ch = xc / NKS;
-            const int xe = min(s1, (ch + 1) * NKS);
+        int cut = 0;  // of the chunk
+        for (int xc = s0; xc < s1;) {  // one chunk, or the part of it with one set of scales
+            const int ch = xc / NKS, run = xc % NKS / RKS;
             const unsigned char *E = ebufs[ch & 1];
             unsigned char *En = ebufs[(ch + 1) & 1];
+            int xe = (ch + 1) * NKS;
+            if (xc == s0 || xc % NKS == 0) cut = scale_changes(E, lane);
+#pragma unroll
+            for (int r = NRUN - 1; r > 0; --r)
+                if (r > run && (cut >> r & 1)) xe = ch * NKS + RKS * r;
+            xe = min(s1, xe);
             // slicing scale of this lane's row: 2^(39 - eA)
-            const int ea = reinterpret_cast<const short *>(E + 256)[16 * (wave >> 1) + li];
+            const int ea = row_exp(E, 16 * (wave >> 1) + li, run);
             const double up = in && ea != kNotFinite ? pow2(39 - ea) : 0.0;
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb)
@@ -555,22 +661,29 @@ __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ 
                 for (int p = 0; p < NSL; ++p)
 #pragma unroll
                     for (int ri = 0; ri < 2; ++ri) acc.g[cb][p][ri] = (int4_t){0, 0, 0, 0};
-            if (xc % NKS) {  // the item starts inside the chunk: the digit sums before it do not belong
-                const global_int *c0 = as_global(S.ec + (size_t)(xc - 1) * NSL * gpad + 16 * NCB * (wave & 1) + li);
+            if (xc % NKS) {  // started inside the chunk: the digit sums before it do not belong
+                const bool at_run = xc % RKS == 0;
+                const int *cl = digit_sums(E, at_run ? run - 1 : 0) + 16 * NCB * (wave & 1) + li;
+                const global_int *cg = as_global(S.ec + (size_t)(xc - 1) * NSL * gpad + 16 * NCB * (wave & 1) + li);
 #pragma unroll
                 for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
                     for (int p = 0; p < NSL; ++p) {
-                        const int c = -c0[p * gpad + 16 * cb];
+                        const int c = at_run ? -cl[p * TC + 16 * cb] : -cg[p * gpad + 16 * cb];
                         acc.g[cb][p][1] = (int4_t){c, c, c, c};
                     }
             }
+            int x = xc;
+            if (x & 1) {
+                split_step(stage1, stage0, En, S, x, s1, up, wave, lane, li, lq, acc);
+                ++x;
+            }
 #pragma unroll 1
-            for (int x = xc; x < xe; x += 2) {  // xc is even: step x uses stage0
+            for (; x < xe; x += 2) {  // step x uses stage x % 2
                 split_step(stage0, stage1, En, S, x, s1, up, wave, lane, li, lq, acc);
                 if (x + 1 < xe) split_step(stage1, stage0, En, S, x + 1, s1, up, wave, lane, li, lq, acc);
             }
-            split_flush(acc, E, wave, li, lq);
+            split_flush(acc, E, (xe - 1) % NKS / RKS, wave, li, lq);
             xc = xe;
         }
 
@@ -708,13 +821,16 @@ size_t split_slices_only_bytes(long long nst, int ng) { return (size_t)nst * NSL
 size_t split_ec_bytes(long long nst, int ng) { return sizeof(int) * (size_t)nst * NSL * split_gpad(ng); }
 
 size_t split_slice_bytes(long long nch, long long nst, int ng) {
-    return split_slices_only_bytes(nst, ng) + split_ec_bytes(nst, ng) + sizeof(short) * (size_t)nch * split_gpad(ng);
+    return split_slices_only_bytes(nst, ng) + split_ec_bytes(nst, ng) +
+           sizeof(short) * NRUN * (size_t)nch * split_gpad(ng);
 }
 
 size_t split_chunk_bytes(int ng) { return split_slice_bytes(1, NKS, ng); }
 
-size_t split_ea_bytes(long long nvec, long long nch, int ng) {
-    return sizeof(short) * (size_t)nvec * nch * split_gpad(ng);
+int split_apad(int ng) { return (ng + 15) / 16 * 16; }
+
+size_t split_ea_bytes(long long nvec, long long nst, int ng) {
+    return (size_t)nvec * ((nst + RKS - 1) / RKS) * split_apad(ng);
 }
 
 // Upper tiles (those with some G <= H) in walk order: bands of eight row
@@ -738,10 +854,10 @@ long long split_wide_tiles(int ng) {
 int split_grid() { return device_cus() / 8 * 8; }
 
 int launch_split_slices(const double2 *M, long long K, int ng, long long c0, int nch, int nst, unsigned char *S,
-                        short *E, const double *w, long long wstride, int nvec, short *EA, int *EC, hipStream_t st) {
+                        short *E, const double *w, long long wstride, int nvec, signed char *EA, int *EC, hipStream_t st) {
     const int gpad = split_gpad(ng);
-    hipLaunchKernelGGL(k_split_slice, dim3(gpad / 32, nch), dim3(SLICE_T), 0, st, M, K, ng, gpad, c0, nch, nst, S, E, w,
-                       wstride, nvec, EA, EC);
+    hipLaunchKernelGGL(k_split_slice, dim3(gpad / 32, nch), dim3(SLICE_T), 0, st, M, K, ng, gpad, c0, nst, S, E, w,
+                       wstride, nvec, EA, split_apad(ng), EC);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
 }
