@@ -389,9 +389,9 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
             base_items += (long long)P.tiles.back().size() * vq;
             wide_items += split_wide_tiles(d->q[iq].ng) * vq;
         }
-        // K splits per q: the wave-filling rule over the whole batch (or the tuned
-        // count), with no more partial sums than tiles a third wider would take: a
-        // workspace limit that fitted those still fits
+        // K splits per q: the tuned count, or the wave-filling rule over the whole batch
+        // with no more partial sums than tiles a third wider (64 x 128, the first form of
+        // this sum) would take: a workspace limit that fitted those still fits
         const long long ns_cap = choose_splits(wide_items, slots, 4, 64);
         P.q_ns.assign(d->nq, 1);
         for (int iq = 0; iq < d->nq; ++iq) {
@@ -415,7 +415,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
         for (int iq = 0; iq < d->nq; ++iq) {
             if (d->q[iq].head >= 0) hw = std::max(hw, sizeof(double2) * (size_t)kHeadSplits * vq * d->q[iq].ng);
             const long long K = q_pairs(d->q[iq]);
-            ew_all += al256(split_ea_bytes(vq, split_steps(K, 0, split_chunks(K)), d->q[iq].ng));
+            ew_all += al256(split_ea_bytes(vq, split_steps(K, 0, split_runs(K)), d->q[iq].ng));
         }
         // slice budget: what the device holds next to everything else of the call
         const size_t other = off + al256(hw) + ew_all + ((size_t)2 << 30);
@@ -424,16 +424,16 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
         if (const char *env = std::getenv("BGW_SPLIT_SLICE_BYTES"))
             budget = std::max<size_t>(1, std::strtoull(env, nullptr, 10));
         // launches: consecutive q whose slices fit together; a q too large alone
-        // is cut into chunk ranges (one launch each, later ones adding)
-        std::vector<std::pair<int, std::pair<long long, long long>>> ranges;  // (q, [c0, c1))
+        // is cut into ranges of runs (one launch each, later ones adding)
+        std::vector<std::pair<int, std::pair<long long, long long>>> ranges;  // (q, [r0, r1))
         for (int iq = 0; iq < d->nq; ++iq) {
-            const long long nch = split_chunks(q_pairs(d->q[iq]));
-            long long fit = nch;
-            if (split_slice_bytes(nch, split_steps(q_pairs(d->q[iq]), 0, nch), d->q[iq].ng) > budget)
-                fit = std::min(nch, std::max<long long>(1, (long long)(budget / split_chunk_bytes(d->q[iq].ng))));
+            const long long nrun = split_runs(q_pairs(d->q[iq]));
+            long long fit = nrun;
+            if (split_slice_bytes(split_steps(q_pairs(d->q[iq]), 0, nrun), d->q[iq].ng) > budget)
+                fit = std::min(nrun, std::max<long long>(1, (long long)(budget / split_run_bytes(d->q[iq].ng))));
             // the first range initialises every split
-            if (fit < nch) fit = std::min(nch, std::max(fit, split_min_chunks(P.q_ns[iq])));
-            for (long long c0 = 0; c0 < nch; c0 += fit) ranges.push_back({iq, {c0, std::min(nch, c0 + fit)}});
+            if (fit < nrun) fit = std::min(nrun, std::max(fit, split_min_runs(P.q_ns[iq])));
+            for (long long r0 = 0; r0 < nrun; r0 += fit) ranges.push_back({iq, {r0, std::min(nrun, r0 + fit)}});
         }
         size_t slice_max = 0, ew_max = 0;
         {
@@ -449,15 +449,15 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
             };
             for (auto &r : ranges) {
                 const int iq = r.first;
-                const long long nchr = r.second.second - r.second.first;
-                const long long nst = split_steps(q_pairs(d->q[iq]), r.second.first, nchr);
-                const size_t b = al256(split_slice_bytes(nchr, nst, d->q[iq].ng));
-                const bool whole = r.second.first == 0 && r.second.second == split_chunks(q_pairs(d->q[iq]));
+                const long long r0 = r.second.first, r1 = r.second.second;
+                const long long nst = split_steps(q_pairs(d->q[iq]), r0, r1 - r0);
+                const size_t b = al256(split_slice_bytes(nst, d->q[iq].ng));
+                const bool whole = r0 == 0 && r1 == split_runs(q_pairs(d->q[iq]));
                 if (!cur.qs.empty() && (!whole || cur_bytes + b > budget)) close();
                 SplitQ e;
                 std::memset(&e, 0, sizeof(e));
-                e.chunk0 = (int)r.second.first;
-                e.nch = (int)nchr;
+                e.run0 = (int)r0;
+                e.nst = (int)nst;
                 cur.qs.push_back(e);
                 cur.qidx.push_back(iq);
                 cur.sb_off.push_back(cur_bytes);
@@ -489,7 +489,6 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
                 e.ntiles = (int)P.tiles[iq].size();
                 // every split non-empty; the first range of a q holds enough steps for q_ns
                 // splits, so it writes all q_ns partial sums that the finalize reads
-                e.nst = (int)split_steps(e.K, e.chunk0, e.nch);
                 e.ns = (int)std::min<long long>(P.q_ns[iq], split_range_ns(e.nst));
                 e.add = seen[iq] ? 1 : 0;
                 seen[iq] = 1;
@@ -628,7 +627,7 @@ int enqueue(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, char *ws, char *t
             Timed tm(h, BGW_KERNEL_SPLIT_SLICE, st);
             for (size_t i = 0; i < L.qs.size(); ++i) {
                 const SplitQ &e = L.qs[i];
-                BGW_TRY(launch_split_slices(e.M, e.K, e.ng, e.chunk0, e.nch, e.nst, (unsigned char *)e.SB, (short *)e.EB, e.w,
+                BGW_TRY(launch_split_slices(e.M, e.K, e.ng, e.run0, e.nst, (unsigned char *)e.SB, (short *)e.EB, e.w,
                                             e.wstride, e.nvec, (signed char *)e.EA, (int *)e.EC, st));
             }
         }

@@ -107,9 +107,8 @@ struct SphereMaps {
 };
 
 // One q of a split-precision chi-sum launch (split.hip), a device table
-// entry.  The launch covers the pair chunks [chunk0, chunk0 + nch) of every
-// entry (384 pairs, twelve k-steps, per chunk) and, per entry, all of its
-// weight vectors.
+// entry.  The launch covers nst k-steps of 32 pairs of every entry from its run run0 (of
+// 96 pairs) on, in chunks of twelve, and, per entry, all of its weight vectors.
 struct SplitQ {
     const double2 *M;          // [K][ng]
     const double *w;           // weight vector v at w + v * wstride, [K] each
@@ -121,7 +120,7 @@ struct SplitQ {
     long long K, wstride, vstride;
     long long item0, nitems;   // work items of this entry (nitems a multiple of 8)
     int ng, gpad, nvec, ntiles;
-    int chunk0, nch;           // chunk range of the launch
+    int run0;                  // first run of the launch
     int nst;                   // its k-steps (32 pairs) that hold pairs < K
     int ns;                    // K splits: with u = ceil(nst / 2), split s takes the steps 2 [s u / ns, (s + 1) u / ns)
     int add;                   // 1: add to the raw sums already in out (later chunk ranges)

@@ -119,22 +119,22 @@ int launch_gemm_finalize(const double2 *part, int ns, long long mn, double scale
                          hipStream_t);
 
 // ---- split-precision launchers (split.hip)
-int split_gpad(int ng);                         // columns of the digit slices (a multiple of the tile width)
-long long split_chunks(long long K);            // chunks (384 pairs each) of K pairs
-long long split_steps(long long K, long long chunk0, long long nch);  // k-steps of a chunk range that hold pairs
+int split_gpad(int ng);                         // columns of the digit slices
+long long split_runs(long long K);              // runs (96 pairs each) of K pairs
+long long split_steps(long long K, long long run0, long long nrun);  // k-steps of a range of runs that hold pairs
 long long split_max_ns(long long K);            // most K splits of K pairs
 long long split_range_ns(long long nst);        // most non-empty K splits of nst k-steps
-long long split_min_chunks(long long ns);       // least full chunks that ns K splits can share
-size_t split_slice_bytes(long long nch, long long nst, int ng);  // slices, digit sums, exponents of nst k-steps
+long long split_min_runs(long long ns);         // least full runs that ns K splits can share
+size_t split_slice_bytes(long long nst, int ng);  // slices, digit sums, exponents of nst k-steps
 size_t split_slices_only_bytes(long long nst, int ng);  // the slices alone (the digit sums follow them)
 size_t split_ec_bytes(long long nst, int ng);   // the digit sums (the exponents follow them)
-size_t split_chunk_bytes(int ng);               // split_slice_bytes of one full chunk
+size_t split_run_bytes(int ng);                 // at least split_slice_bytes per run of more runs
 int split_apad(int ng);                         // columns of the weighted-side exponents
 size_t split_ea_bytes(long long nvec, long long nst, int ng);  // weighted-side exponents of nst k-steps
 void split_tiles(int ng, std::vector<unsigned> &out);  // upper 64 x 96 tiles in walk order
 long long split_wide_tiles(int ng);             // upper tiles if they were 64 x 128
 int split_grid();                               // blocks of the persistent split launch
-int launch_split_slices(const double2 *M, long long K, int ng, long long c0, int nch, int nst, unsigned char *S,
+int launch_split_slices(const double2 *M, long long K, int ng, long long r0, int nst, unsigned char *S,
                         short *E, const double *w, long long wstride, int nvec, signed char *EA, int *EC, hipStream_t);
 int launch_chi_split(const SplitQ *qs, int nq, long long nitems, hipStream_t);
 int launch_headwing(const double2 *M, long long K, int ng, int head, const double *w, long long wstride, int nvec,

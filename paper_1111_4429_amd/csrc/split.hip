@@ -63,6 +63,7 @@ constexpr int NKS = 12;       // k-steps per chunk
 constexpr int SKP = KSP * NKS; // pairs per chunk
 constexpr int RKS = 3;        // k-steps per run (96 pairs, one exponent per column)
 constexpr int NRUN = NKS / RKS;
+constexpr int RP = RKS * KSP; // pairs per run
 constexpr int SLACK_A = 3, SLACK_B = 1;  // powers of two by which a run may lie below the scale it shares
 constexpr int UKS = 2;        // K splits are cut at multiples of this many k-steps
 constexpr int KSB = 2 * KSP;  // bytes of one column's digits of one slice and k-step
@@ -150,8 +151,8 @@ __device__ __forceinline__ double abs_max(double2 z) {
 }
 }  // namespace
 
-// Digit slices of the unweighted side for chunks [c0, c0 + nchunk) of one q,
-// and the exponents of the weighted side of every weight vector.
+// Digit slices of the unweighted side for the first nst k-steps (those that hold pairs <
+// K) from run r0 of one q on, chunks counted from there, and the exponents of the weighted side of every weight vector.
 // Block = one chunk x 32 columns, 768 threads.  Thread t owns column G = 32
 // blockIdx.x + (t/4) % 32 and, in each of the k-steps 2 (t/128) and
 // 2 (t/128) + 1, the eight pairs 8 (t%4) .. +7; with this assignment every
@@ -161,11 +162,11 @@ __device__ __forceinline__ double abs_max(double2 z) {
 // [nvec][runs][apad], eA - eB (within a byte: the size of the weights; below 2^-128 a
 // weight keeps fewer digits, above 2^126 it counts as not finite).
 // EC: [k-step][NSL][gpad], entry p the sum of the Re digits 0
-// .. p of the column over the chunk's k-steps up to this one.  Pairs >= K are
-// zero; only the first nst k-steps, those that hold pairs < K, are stored.
+// .. p of the column over the chunk's k-steps up to this one.  Pairs >= K are zero.
+// gpad: ng rounded up to 32 (this block), apad to 16 (a load of the GEMM).
 constexpr int SLICE_T = 32 * 4 * (NKS / 2);  // 768
 __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restrict__ M, long long K, int ng, int gpad,
-                                                         long long c0, int nst, unsigned char *__restrict__ S,
+                                                         long long r0, int nst, unsigned char *__restrict__ S,
                                                          short *__restrict__ E, const double *__restrict__ w,
                                                          long long wstride, int nvec, signed char *__restrict__ EA,
                                                          int apad, int *__restrict__ EC) {
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restri
     const int q = threadIdx.x & 3, cl = (threadIdx.x >> 2) & 31, kh = threadIdx.x >> 7;
     const int G = blockIdx.x * 32 + cl;
     const int chunk = blockIdx.y;
-    const long long tb = (c0 + chunk) * SKP + 2 * kh * KSP + 8 * q;  // k-step i, pair j: tb + KSP i + j
+    const long long tb = r0 * RP + (long long)chunk * SKP + 2 * kh * KSP + 8 * q;  // k-step i, pair j: tb + KSP i + j
     const bool col = G < ng;
     // the first 128 threads reduce: thread t run t % 4 of column t / 4 (its cl)
     const bool reduces = threadIdx.x < 32 * NRUN;
@@ -340,6 +341,7 @@ struct StageSrc {
     const char *b;           // slices
     unsigned b_slice;        // bytes of one slice of a k-step: gpad * KSB
     unsigned b0;             // the tile's first column in it
+    int b_last;              // last 16 columns of it from there on that are stored
     int b_off;               // lane L of a piece: row L/4, source segment (L%4) ^ ((L/8) & 3)
     const double *w;         // weights of this vector at the launch's first pair
     const short *eb;         // EB: exponents of the slices, [nch][gpad][NRUN]
@@ -350,7 +352,8 @@ struct StageSrc {
 
 // One k-step x into one stage.  A piece i of wave w is pair row 4w + i of the
 // k-step (past K the last pair again: it meets zero digits of the other side);
-// B piece p = w + 8 i is slice p / 6, rows 16 (p % 6) .. +16.  Wave 7 loads the
+// B piece p = w + 8 i is slice p / 6, rows 16 (p % 6) .. +16 (past gpad,
+// where no sums are stored, the last ones again).  Wave 7 loads the
 // step's weights (two per lane, four times over; the vectors are padded by 128
 // entries) and wave 6 the exponents of the step's chunk when they are new.
 __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, unsigned char *__restrict__ ebuf,
@@ -372,7 +375,7 @@ __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, u
         if ((i + 1) * NWAVE <= NB_PIECES || p < NB_PIECES)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 rb, (lds_void_t *)(stage + A_LDS + p * 1024), 16, S.b_off,
-                (int)(S.b0 + (p / (TC / 16)) * S.b_slice + (p % (TC / 16)) * 1024), 0, 0);
+                (int)(S.b0 + (p / (TC / 16)) * S.b_slice + min(p % (TC / 16), S.b_last) * 1024), 0, 0);
     }
     if (wave == NWAVE - 1) {
         __builtin_amdgcn_global_load_lds((const void *)(S.w + t0 + 2 * (lane & 15)), (lds_void_t *)(stage + W_OFF), 16, 0,
@@ -395,7 +398,8 @@ __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, u
             const int i = min(64 * h + l, NRUN * EC_RUN / 16 - 1);  // 16 bytes: four columns of an entry of a run
             const int last = min(S.s1, ch * NKS + RKS * (i / (EC_RUN / 16) + 1)) - 1, j = i % (EC_RUN / 16);
             __builtin_amdgcn_global_load_lds(
-                (const void *)(S.ec + ((size_t)last * NSL + j / (TC / 4)) * S.gpad + j % (TC / 4) * 4),
+                (const void *)(S.ec + ((size_t)last * NSL + j / (TC / 4)) * S.gpad +
+                               min(j % (TC / 4) * 4, S.gpad - S.H0 - 4)),
                 (lds_void_t *)(ebuf + EC_OFF + h * 1024), 16, 0, 0);
         }
     }
@@ -607,14 +611,15 @@ __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ 
 
         StageSrc S;
         S.m_row = (unsigned)ng * 16;
-        S.m = reinterpret_cast<const char *>(Q.M) + (long long)Q.chunk0 * SKP * S.m_row;
+        S.m = reinterpret_cast<const char *>(Q.M) + (long long)Q.run0 * RP * S.m_row;
         S.m_off = min(G0 + lane, ng - 1) * 16;
-        S.kmax = Q.K - 1 - (long long)Q.chunk0 * SKP;
+        S.kmax = Q.K - 1 - (long long)Q.run0 * RP;
         S.b = reinterpret_cast<const char *>(Q.SB);
         S.b_slice = (unsigned)gpad * KSB;
         S.b0 = (unsigned)H0 * KSB;
+        S.b_last = (gpad - H0) / 16 - 1;
         S.b_off = (lane >> 2) * KSB + 16 * ((lane & 3) ^ ((lane >> 3) & 3));
-        S.w = Q.w + (size_t)v * Q.wstride + (long long)Q.chunk0 * SKP;
+        S.w = Q.w + (size_t)v * Q.wstride + (long long)Q.run0 * RP;
         S.eb = Q.EB;
         S.nrun = (Q.nst + RKS - 1) / RKS;
         S.apad = Q.apad;
@@ -664,12 +669,15 @@ __global__ __launch_bounds__(XT, 1) void k_chi_split(const SplitQ *__restrict__ 
             if (xc % NKS) {  // started inside the chunk: the digit sums before it do not belong
                 const bool at_run = xc % RKS == 0;
                 const int *cl = digit_sums(E, at_run ? run - 1 : 0) + 16 * NCB * (wave & 1) + li;
-                const global_int *cg = as_global(S.ec + (size_t)(xc - 1) * NSL * gpad + 16 * NCB * (wave & 1) + li);
+                const global_int *cg = as_global(S.ec + (size_t)(xc - 1) * NSL * gpad);
+                int c0 = 16 * NCB * (wave & 1) + li;
+                asm volatile("" : "+v"(c0));  // (as in stage_issue)
 #pragma unroll
                 for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
                     for (int p = 0; p < NSL; ++p) {
-                        const int c = at_run ? -cl[p * TC + 16 * cb] : -cg[p * gpad + 16 * cb];
+                        const int c =
+                            at_run ? -cl[p * TC + 16 * cb] : -cg[p * gpad + min(c0 + 16 * cb, gpad - H0 - 1)];
                         acc.g[cb][p][1] = (int4_t){c, c, c, c};
                     }
             }
@@ -800,32 +808,33 @@ int device_cus() {
     return cus;
 }
 
-int split_gpad(int ng) { return (ng + TC - 1) / TC * TC; }
+int split_gpad(int ng) { return (ng + 31) / 32 * 32; }
 
-long long split_chunks(long long K) { return (K + SKP - 1) / SKP; }
+long long split_runs(long long K) { return (K + RP - 1) / RP; }
 
-long long split_steps(long long K, long long chunk0, long long nch) {
-    return std::min(nch * NKS, (K - chunk0 * SKP + KSP - 1) / KSP);
+long long split_steps(long long K, long long run0, long long nrun) {
+    return std::min(nrun * RKS, (K - run0 * RP + KSP - 1) / KSP);
 }
 
-// A split keeps at least three k-steps (96 pairs): its partial sums cost as much
-// as they save below that.
-long long split_max_ns(long long K) { return (K + 3 * KSP - 1) / (3 * KSP); }
+// A split keeps at least a run (96 pairs): its partial sums cost as much as they save
+// below that.
+long long split_max_ns(long long K) { return split_runs(K); }
 
 long long split_range_ns(long long nst) { return (nst + UKS - 1) / UKS; }
 
-long long split_min_chunks(long long ns) { return (ns * UKS + NKS - 1) / NKS; }
+long long split_min_runs(long long ns) { return (ns * UKS - 1 + RKS - 1) / RKS; }
 
 size_t split_slices_only_bytes(long long nst, int ng) { return (size_t)nst * NSL * KSB * split_gpad(ng); }
 
 size_t split_ec_bytes(long long nst, int ng) { return sizeof(int) * (size_t)nst * NSL * split_gpad(ng); }
 
-size_t split_slice_bytes(long long nch, long long nst, int ng) {
+size_t split_slice_bytes(long long nst, int ng) {
+    const long long nch = (nst + NKS - 1) / NKS;
     return split_slices_only_bytes(nst, ng) + split_ec_bytes(nst, ng) +
            sizeof(short) * NRUN * (size_t)nch * split_gpad(ng);
 }
 
-size_t split_chunk_bytes(int ng) { return split_slice_bytes(1, NKS, ng); }
+size_t split_run_bytes(int ng) { return split_slice_bytes(RKS, ng); }
 
 int split_apad(int ng) { return (ng + 15) / 16 * 16; }
 
@@ -853,10 +862,10 @@ long long split_wide_tiles(int ng) {
 
 int split_grid() { return device_cus() / 8 * 8; }
 
-int launch_split_slices(const double2 *M, long long K, int ng, long long c0, int nch, int nst, unsigned char *S,
+int launch_split_slices(const double2 *M, long long K, int ng, long long r0, int nst, unsigned char *S,
                         short *E, const double *w, long long wstride, int nvec, signed char *EA, int *EC, hipStream_t st) {
-    const int gpad = split_gpad(ng);
-    hipLaunchKernelGGL(k_split_slice, dim3(gpad / 32, nch), dim3(SLICE_T), 0, st, M, K, ng, gpad, c0, nst, S, E, w,
+    const int gpad = split_gpad(ng), nch = (nst + NKS - 1) / NKS;
+    hipLaunchKernelGGL(k_split_slice, dim3(gpad / 32, nch), dim3(SLICE_T), 0, st, M, K, ng, gpad, r0, nst, S, E, w,
                        wstride, nvec, EA, split_apad(ng), EC);
     BGW_HIP(hipGetLastError());
     return BGW_OK;
