@@ -394,8 +394,11 @@ int bgw_eps_inv(bgw_handle_t h, int ng, int nw, const double *vcoul, const doubl
  * with v > 0.  Then epsilon = S (1 - S chi S) S^-1 with S = diag(v^1/2), the
  * middle factor Hermitian with eigenvalues >= 1, so every elimination pivot
  * is real and >= 1 and the elimination needs no row interchanges: only the
- * 64 x 64 diagonal block of each panel is eliminated column by column, the
- * rest is parallel.  Same arguments and results (to rounding) as
+ * 64 x 64 diagonal block of each panel is serial (by blocks of 16), the rest is
+ * parallel.  A chi Hermitian to the last bit, as bgw_chi0 writes it, is read and
+ * eliminated on and above the diagonal only, in half the operations; one
+ * Hermitian only to the 1e-8 below as a general matrix, both triangles as they
+ * are.  Same arguments and results (to rounding) as
  * bgw_eps_inv.  The precondition is checked: info[w] = -2 when chi[w] is
  * not Hermitian to 1e-8 relative on the scale sqrt(v_G v_G') (or some v <= 0,
  * or a value is not finite), -3 when a pivot has real part below 1/2 or is

@@ -1141,9 +1141,10 @@ int gje_max_group(int n) {
 // only: half the products.  W = Dinv R of the panel's rows R is also, conjugate
 // transposed, the panel's columns, so that both operands of the update lie in rows.
 // k_nsd_unscale makes the whole eps^-1 of it.  A matrix that is Hermitian only to
-// 1e-8, not to 2^-50 of its largest element (a few roundings; the lower triangle
-// then holds information of its own), is eliminated in general form, as eps, by
-// the same launches; which of the two is decided on the device, from k_nsd_check.
+// 1e-8, not to the last bit (the lower triangle then holds information of its own; chi
+// of the chi sum is, but not every product that is Hermitian on paper), is
+// eliminated in general form, as eps, by the same launches; which of the two is
+// decided on the device, from k_nsd_check.
 // A matrix whose chi is not Hermitian to 1e-8 (relative, on the symmetrised
 // scale) or has v <= 0 gets info = -2; one with a pivot whose real part is
 // below 1/2, or that is not real to half of it, gets info = -3 (chi not
@@ -1201,6 +1202,7 @@ __global__ __launch_bounds__(256) void k_nsd_check(const double2 *__restrict__ c
             double d = sc * sqrt((x.x - y.x) * (x.x - y.x) + (x.y + y.y) * (x.y + y.y));
             double m = sc * fmax(sqrt(x.x * x.x + x.y * x.y), sqrt(y.x * y.x + y.y * y.y));
             if (!(vi > 0.0) || !(vj > 0.0) || !(d <= DBL_MAX) || !(m <= DBL_MAX)) d = m = INFINITY;
+            if (x.x != y.x || x.y != -y.y) d = fmax(d, DBL_MIN);  // zero only where the two are equal
             nh = fmax(nh, d);
             mx = fmax(mx, m);
         }
@@ -1225,10 +1227,11 @@ __global__ __launch_bounds__(256) void k_nsd_check(const double2 *__restrict__ c
     }
 }
 
-// The form a matrix takes (see above): Hermitian to 2^-50 of its scale, or general.
+// The form a matrix takes (see above): Hermitian to the last bit, or general.  (To a few
+// roundings of the largest element is not enough: with a head of v(q0 + 0) the small
+// elements of the lower triangle then hold more than their rounding.)
 __device__ __forceinline__ bool nsd_hermitian(const double *chk, int mat) {
-    const double nh = chk[2 * mat], mx = chk[2 * mat + 1];
-    return mx <= DBL_MAX && nh <= 0x1p-50 * mx;
+    return chk[2 * mat] == 0.0 && chk[2 * mat + 1] <= DBL_MAX;
 }
 
 // epst (every 64-block on or above the diagonal) or eps.  One row per workgroup, grid
