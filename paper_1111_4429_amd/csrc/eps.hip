@@ -1407,21 +1407,25 @@ __global__ __launch_bounds__(kNsdDiagThreads) void k_nsd_diag(double2 *__restric
             }
             __syncthreads();
         }
-        // block (a, b): -D[a, k] Dk at b = k, else D[a, b] - D[a, k] W[b]
+        // block (a, b): -D[a, k] Dk at b = k, else D[a, b] - D[a, k] W[b] (the product summed by
+        // itself and added once: summed onto D, each MFMA would round at D's size)
         const int a = (k + 1 + wave / 4) & 3, b = (k + 1 + wave % 4) & 3;
-        double4_t re, im;
+        double4_t re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+        double2 old[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const double2 x = D[(16 * a + 4 * r + lk) * kNsdNb + 16 * b + li];
-            re[r] = b == k ? 0.0 : x.x;
-            im[r] = b == k ? 0.0 : x.y;
-        }
+        for (int r = 0; r < 4; ++r)
+            old[r] = b == k ? make_double2(0.0, 0.0) : D[(16 * a + 4 * r + lk) * kNsdNb + 16 * b + li];
         if (k >= 0) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const double2 x = Cb[(16 * a + li) * LD + 4 * t + lk];
                 cmfma(re, im, make_double2(-x.x, -x.y), D[(16 * k + 4 * t + lk) * kNsdNb + 16 * b + li]);
             }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            re[r] += old[r].x;
+            im[r] += old[r].y;
         }
         if (wave == 0 && k + 1 < nk) {  // the next diagonal block (4 r + lk, li), inverted into Dk
             double2 d[4];
@@ -1548,9 +1552,10 @@ __global__ __launch_bounds__(256) void k_nsd_rows(double2 *__restrict__ A, int n
         }
         return;
     }
-    // the second product: MODE 1 R2 - D21 W1, MODE 2 W1 - (D1 D12) W2 (in every lane: the
-    // a of a lane past n is other lanes' operand)
+    // the second product, summed by itself and then added: MODE 1 R2 - D21 W1, MODE 2 W1 -
+    // (D1 D12) W2 (in every lane: the a of a lane past n is other lanes' operand)
     double4_t re2 = {0.0, 0.0, 0.0, 0.0}, im2 = {0.0, 0.0, 0.0, 0.0};
+    double2 old[4];
     const bool in1 = g0 >= k && g0 < K2, in2 = g0 >= K2 && g0 < ke;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -1565,8 +1570,7 @@ __global__ __launch_bounds__(256) void k_nsd_rows(double2 *__restrict__ A, int n
         } else if (live && !in2) {
             x = Am[(size_t)(k + t) * n + g];
         }
-        re2[r] = x.x;
-        im2[r] = x.y;
+        old[r] = x;
     }
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
@@ -1584,7 +1588,7 @@ __global__ __launch_bounds__(256) void k_nsd_rows(double2 *__restrict__ A, int n
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int t = T0 + 4 * r + lk;
-        const double2 w = make_double2(re[r], im[r]), x = make_double2(re2[r], im2[r]);
+        const double2 w = make_double2(re[r], im[r]), x = make_double2(old[r].x + re2[r], old[r].y + im2[r]);
         if (!live) continue;
         if (MODE == 1) {
             if (t < nb2) Am[(size_t)(K2 + t) * n + g] = x;
