@@ -127,3 +127,19 @@ def test_exchange_kernel(torch_dev, spread):
     up = np.triu(bound(M.T.copy(), v, 0.5))
     up = up + np.triu(up, 1).T
     assert np.all(np.abs(got - ref) <= up)
+
+
+def test_advanced_is_the_adjoint(torch_dev):
+    """Weights, digits and INT32 sums are the same on both real axes: chi^a is chi^r's
+    adjoint to the last bit."""
+    rng = np.random.default_rng(4)
+    nk, nv, nc, ng = 2, 3, 83, 130
+    dev = lambda a: torch_dev.from_numpy(np.ascontiguousarray(a)).to("cuda:0")  # noqa: E731
+    q = dict(M=dev(columns(rng, nk * nv * nc, ng, 8.0)), ev=dev(np.sort(rng.uniform(-5, 0, (nk, nv)))),
+             ec=dev(np.sort(rng.uniform(0.5, 9, (nk, nc)))), nk=nk, nv=nv, nc=nc, head=0, prefactor=0.5)
+    h = bgw.Handle(0)
+    r, a = (h.chi0([q], [0.0, 2.0, 7.0], precision=bgw.SPLIT_BF16, axis=x, broadening=0.2)[0]
+            for x in ("retarded", "advanced"))
+    torch_dev.cuda.synchronize()
+    h.close()
+    assert torch_dev.equal(a, r.mH.contiguous())
