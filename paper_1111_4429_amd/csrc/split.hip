@@ -165,27 +165,33 @@ __device__ __forceinline__ double abs_max(double2 z) {
 // .. p of the column over the chunk's k-steps up to this one.  Pairs >= K are zero.
 // gpad: ng rounded up to 32 (this block), apad to 16 (a load of the GEMM).
 constexpr int SLICE_T = 32 * 4 * (NKS / 2);  // 768
+constexpr int SLICE_V = 4;                   // weight vectors per round
 __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restrict__ M, long long K, int ng, int gpad,
                                                          long long r0, int nst, unsigned char *__restrict__ S,
                                                          short *__restrict__ E, const double *__restrict__ w,
                                                          long long wstride, int nvec, signed char *__restrict__ EA,
                                                          int apad, int *__restrict__ EC) {
     constexpr int NP = 4 * RKS;        // partial maxima per column and run
-    __shared__ double red[4 * NKS][33];
-    __shared__ int ex[NRUN][32];
+    __shared__ double red[SLICE_V][4 * NKS][33];
+    __shared__ int ex[NRUN][32], changed[SLICE_V][NRUN][32];
     __shared__ int dsum[NKS][NSL][32];
+    __shared__ double wa[SLICE_V][SKP];  // |w| of the chunk's pairs
+    __shared__ int wbad[SLICE_V][NRUN];  // a weight of the run is not finite
     const int q = threadIdx.x & 3, cl = (threadIdx.x >> 2) & 31, kh = threadIdx.x >> 7;
     const int G = blockIdx.x * 32 + cl;
     const int chunk = blockIdx.y;
     const long long tb = r0 * RP + (long long)chunk * SKP + 2 * kh * KSP + 8 * q;  // k-step i, pair j: tb + KSP i + j
     const bool col = G < ng;
-    // the first 128 threads reduce: thread t run t % 4 of column t / 4 (its cl)
-    const bool reduces = threadIdx.x < 32 * NRUN;
-    auto run_max = [&]() {
+    // 128 threads reduce: thread t run t % 4 of column t / 4 (its cl), for the vector t / 128 of a round
+    auto run_max = [&](int v) {
         double mx = 0.0;
 #pragma unroll
-        for (int k = 0; k < NP; ++k) mx = fmax(mx, red[NP * q + k][cl]);
+        for (int k = 0; k < NP; ++k) mx = fmax(mx, red[v][NP * q + k][cl]);
         return mx;
+    };
+    auto changes = [&](int e) {  // from the run before to this thread's
+        const int before = __shfl_up(e, 1, 64);
+        return q > 0 && before != e;
     };
     double2 m[2][8];  // [k-step i][pair j]
     double mr[2][8];
@@ -204,19 +210,12 @@ __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restri
             mr[i][j] = abs_max(m[i][j]);
             mx = fmax(mx, mr[i][j]);
         }
-        red[4 * (2 * kh + i) + q][cl] = mx;
+        red[0][4 * (2 * kh + i) + q][cl] = mx;
     }
     __syncthreads();
-    int eb = 0, own = 0, any = 0;  // of the reducing threads' runs: eB, and whether a scale changes there
-    auto changes = [&](int e) {
-        const int before = __shfl_up(e, 1, 64);
-        return q > 0 && before != e;
-    };
-    if (reduces) {
-        eb = quad_run_exp(run_max(), SLACK_B);
-        if (eb == kZeroRun) eb = 0;
-        own = changes(eb);
-        ex[q][cl] = eb;
+    if (kh == 0) {
+        const int e = quad_run_exp(run_max(0), SLACK_B);
+        ex[q][cl] = e == kZeroRun ? 0 : e;
     }
     __syncthreads();
 #pragma unroll
@@ -251,41 +250,67 @@ __global__ __launch_bounds__(SLICE_T) void k_split_slice(const double2 *__restri
     if (threadIdx.x < NSL * 32) {  // one thread per entry and column: running sums over the k-steps
         const int sl = threadIdx.x >> 5, c = threadIdx.x & 31;
         int run = 0;
-        for (int ks = 0; ks < min(NKS, nst - chunk * NKS); ++ks) {
-            for (int j = 0; j <= sl; ++j) run += dsum[ks][j][c];
-            EC[(((size_t)chunk * NKS + ks) * NSL + sl) * gpad + blockIdx.x * 32 + c] = run;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+#pragma unroll
+            for (int j = 0; j < NSL; ++j) run += j <= sl ? dsum[ks][j][c] : 0;
+            if (chunk * NKS + ks < nst)
+                EC[(((size_t)chunk * NKS + ks) * NSL + sl) * gpad + blockIdx.x * 32 + c] = run;
         }
     }
-    // weighted side: |w| max(|Re M|, |Im M|) bounds the products the GEMM rounds
-    const int nrun = (nst + RKS - 1) / RKS, run = chunk * NRUN + q;
-    for (int v = 0; v < nvec; ++v) {
-        const double *wv = w + (size_t)v * wstride;
-        __syncthreads();  // the previous reduction has been read
+    // weighted side: |w| max(|Re M|, |Im M|) bounds the products the GEMM rounds.  Four vectors a
+    // round, their weights through LDS: a small call has few blocks, each of which goes through
+    // all vectors (100 vectors, 1000 pairs, 32 frequencies: 125 us with the weights loaded by
+    // every thread, 37 now).
+    const int nrun = (nst + RKS - 1) / RKS, run = chunk * NRUN + q, eb = ex[q][cl];
+    bool any = false;
+    for (int v0 = 0; v0 < nvec; v0 += SLICE_V) {
+        __syncthreads();  // the previous round has been read
+        if (threadIdx.x < SLICE_V * NRUN) (&wbad[0][0])[threadIdx.x] = 0;
+        double wt[SLICE_V / 2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            double mw = 0.0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const long long t = tb + KSP * i + j;
-                if (t < K && col) {
-                    const double x = fabs(wv[t]) * mr[i][j];
-                    mw = x <= 1.7e308 ? fmax(mw, x) : INFINITY;
-                }
-            }
-            red[4 * (2 * kh + i) + q][cl] = mw;
+        for (int i = 0; i < SLICE_V / 2; ++i) {
+            const int v = v0 + 2 * i + (int)threadIdx.x / SKP, p = (int)threadIdx.x % SKP;
+            const long long t = r0 * RP + (long long)chunk * SKP + p;
+            wt[i] = v < nvec && t < K ? fabs(w[(size_t)v * wstride + t]) : 0.0;
         }
         __syncthreads();
-        if (reduces) {
-            const int e = quad_run_exp(run_max(), SLACK_A);
+#pragma unroll
+        for (int i = 0; i < SLICE_V / 2; ++i) {
+            const int v = 2 * i + (int)threadIdx.x / SKP, p = (int)threadIdx.x % SKP;
+            wa[v][p] = wt[i];
+            if (!(wt[i] <= 1.7e308)) wbad[v][p / RP] = 1;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < SLICE_V; ++v)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const double *wi = &wa[v][(2 * kh + i) * KSP + 8 * q];
+                double mw = 0.0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) mw = fmax(mw, wi[j] * mr[i][j]);
+                red[v][4 * (2 * kh + i) + q][cl] = mw;
+            }
+        __syncthreads();
+        if (kh < SLICE_V && v0 + kh < nvec) {
+            const bool bad = wbad[kh][q] || eb == kNotFinite;  // (0 times infinity is lost in the maximum)
+            const int e = quad_run_exp(bad ? INFINITY : run_max(kh), SLACK_A);
             int rel = e == kZeroRun ? 0 : max(e - eb, -128);
             if (e == kNotFinite || rel >= kNotFiniteA) rel = kNotFiniteA;
             any |= changes(eb + rel);
-            if (run < nrun && G < apad) EA[((size_t)v * nrun + run) * apad + G] = (signed char)rel;
+            if (run < nrun && G < apad) EA[((size_t)(v0 + kh) * nrun + run) * apad + G] = (signed char)rel;
         }
     }
-    if (reduces)
+    if (kh < SLICE_V) changed[kh][q][cl] = any;
+    __syncthreads();
+    if (kh == 0) {
+        const bool own = changes(eb);
+#pragma unroll
+        for (int v = 1; v < SLICE_V; ++v) any |= changed[v][q][cl] != 0;
         E[((size_t)chunk * gpad + G) * NRUN + q] =
             (short)((eb + kExpBias) | (own ? kOwnChange : 0) | (own || any ? kAnyChange : 0));
+    }
 }
 
 namespace {

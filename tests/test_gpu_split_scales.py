@@ -143,3 +143,33 @@ def test_advanced_is_the_adjoint(torch_dev):
     torch_dev.cuda.synchronize()
     h.close()
     assert torch_dev.equal(a, r.mH.contiguous())
+
+
+@pytest.mark.parametrize("nw", [3, 4, 5, 9])
+def test_vectors_of_a_round(torch_dev, nw):
+    """Exponents of the weighted side are found four vectors a round: counts around
+    that, on weights of different ranges, and one that is not finite spoils its own
+    vector only."""
+    rng = np.random.default_rng(nw)
+    K, ng = 450, 70
+    M = columns(rng, K, ng, 6.0)
+    ev, ec = np.array([[-0.5]]), np.sort(np.exp(rng.uniform(0.0, 5.0, (1, K))))
+    om = np.concatenate([[0.0], np.exp2(rng.uniform(-3.0, 7.0, nw - 1))])
+    dev = lambda a: torch_dev.from_numpy(np.ascontiguousarray(a)).to("cuda:0")  # noqa: E731
+    h = bgw.Handle(0)
+    q = dict(M=dev(M), ev=dev(ev), ec=dev(ec), nk=1, nv=1, nc=K, head=-1, prefactor=0.5)
+    (chi,) = h.chi0([q], om, precision=bgw.SPLIT_BF16)
+    w = oracle.weights(ev, ec, om)
+    ref = oracle.chi(M, w, 0.5)
+    got = chi.cpu().numpy()
+    for i in range(nw):
+        up = np.triu(bound(M, w[i], 0.5))
+        up = up + np.triu(up, 1).T
+        assert np.all(np.abs(got[i] - ref[i]) <= up)
+    ec[0, 200] = ev[0, 0]  # Delta = 0: the static weight is infinite, the others are zero
+    (chi,) = h.chi0([dict(q, ec=dev(ec))], om, precision=bgw.SPLIT_BF16)
+    torch_dev.cuda.synchronize()
+    got = chi.cpu().numpy()
+    h.close()
+    assert not np.isfinite(got[0].real).any()
+    assert np.isfinite(got[1:]).all()
