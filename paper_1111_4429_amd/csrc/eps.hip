@@ -1757,6 +1757,7 @@ int launch_nsd_invert(double2 *A, const double *v, int n, int nmat, int m0, int 
         const int nb = std::min(kNsdNb, ke - k), nb2 = ke - K2;
         hipLaunchKernelGGL(k_nsd_diag, dg, tdiag, 0, st, A, n, k, nb, w.Dinv, chk, info);
         if (nb2 <= 0) {
+            if (n <= nb) break;  // one panel is the whole matrix
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_nsd_rows<0>), rg, t256, 0, st, A, n, k, ke, k, nb, w.Dinv, Rs, nbo, chk);
         } else {
             hipLaunchKernelGGL(HIP_KERNEL_NAME(k_nsd_rows<1>), rg, t256, 0, st, A, n, k, ke, k, nb, w.Dinv, Rs, nbo, chk);
