@@ -85,7 +85,7 @@ void chi_state_free(ChiState *s) { delete s; }
 namespace {
 
 constexpr size_t kMaxGraphs = 64;
-constexpr int kHerkKC = 16;  // pairs per LDS stage of the FP64 kernel (split ranges are multiples of it)
+constexpr int kHerkKC = 16;  // K splits of the FP64 kernel are multiples of this many pairs (two of its LDS stages)
 
 ChiState *state(bgw_handle_t h) {
     if (!h->chi) h->chi = new ChiState();
@@ -282,7 +282,7 @@ int make_plan(bgw_handle_t h, const bgw_chi_desc *d, ChiPlan &P, int force_tile,
                                        : (part == 0 ? kWeightRealRe : kWeightRetIm);
                 P.wts.push_back(wp);
                 P.w_off.push_back(off);
-                off += al256(sizeof(double) * (K + 128));  // padded: the split GEMM stages whole 16-pair steps
+                off += al256(sizeof(double) * (K + 128));  // padded: the split GEMM loads whole steps of 32 pairs
             }
     }
     size_t free_b = 0, total_b = 0;

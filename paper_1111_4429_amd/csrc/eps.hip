@@ -533,9 +533,9 @@ __global__ __launch_bounds__(256) void k_gje_swap_save(double2 *__restrict__ A, 
 // A[:, cs] += P * R with P = A[:, r0:r0+nbr] (n x nbr) and R = Rs (nbr x m); the
 // old values of the tile are fetched under the last stage's MFMAs.  Bound by the
 // FP64 MFMAs at 128 columns per update (16 flops per byte of A moved) and by
-// latency in the narrow updates within an outer block.  Four matrices of 4000
-// without interchanges, whole inversions: 48.0 -> 41.3 ms against a tile loop that
-// staged both operands through registers.
+// latency in the narrow updates within an outer block.  Eight matrices of 1500, whole
+// inversions: 13.88 -> 13.02 ms against a tile loop that staged both operands through
+// registers (11.3 with what the panels and interchanges have saved since).
 template <int T>
 __global__ __launch_bounds__(256, 2) void k_gje_update(double2 *__restrict__ A, int n, int r0, int nbr, GjeCols cs,
                                                     const double2 *__restrict__ Rs) {
@@ -936,11 +936,13 @@ static void launch_gje_update_t(double2 *A, int n, int nmat, int r0, int nbr, Gj
                        dim3(256), 0, st, A, n, r0, nbr, cs, Rs);
 }
 
-// 64-wide tiles read half as much per product; below 2000 of them (eight per
-// CU) the last ones leave most of the chip idle, and 32-wide tiles finish first:
-// one matrix of 1500, 64 columns per update (576 tiles), 2.49 ms in 64-wide tiles
-// for the whole inversion, 2.35 in 32-wide ones; four of 4000 (15876 tiles) 41.3
-// and 43.8 ms.
+// 64-wide tiles read half as much per product; of fewer than 2000 of them (eight per
+// CU) the last ones leave most of the chip idle, and 32-wide tiles finish first.
+// Whole inversions in 64- and in 32-wide tiles, with the tiles of an outer block's
+// update: one matrix of 1500 (552) 7.19 and 6.76 ms, one of 2500 (1560) 24.76 and
+// 24.03, four of 1500 (2208) 8.79 and 8.46, one of 3100 (2303) 31.84 and 31.73, two of
+// 3100 (4606) 37.73 and 37.88, four of 4000 (15372) 83.0 and 86.2; the updates within
+// an outer block, of fewer columns, are in 32-wide tiles at all of these but the last.
 static void launch_gje_update(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, const double2 *Rs,
                               hipStream_t st) {
     const long long t64 = (long long)((n + 63) / 64) * ((cs.count() + 63) / 64) * nmat;
@@ -1155,7 +1157,10 @@ int gje_max_group(int n) {
 // Four matrices of 4000: 41.3 -> 22.6 ms, 17.2 of them in the update at 61 TFLOP/s
 // of FP64 MFMA.  k_nsd_diag: 51 -> 23 us; its 64 pivots take 7.5 us of that (one
 // wave, no LDS round trip or barrier per pivot), the MFMA steps 5, loads, stores
-// and the launch the rest.  k_nsd_rows: 12.3 -> 8 us at n = 1500.
+// and the launch the rest.  k_nsd_rows: 12.3 -> 8 us at n = 1500.  The general form takes
+// twice the products: 1500 2.69 -> 1.47 ms, eight of 1500 7.59 -> 6.02, four of 4000 48.0
+// -> 38.0.  (The Hermitian form's two k_nsd_inner launches per two panels, which return
+// at once, are 0.2 of its 22.5 ms there.)
 constexpr int kNsdNb = 64;        // panel width (diagonal block size)
 constexpr int kNsdDiagThreads = 768;
 constexpr int kNsdTile = 32;      // tile of the Hermitian check and of the unscaling
@@ -1749,8 +1754,10 @@ int launch_nsd_invert(double2 *A, const double *v, int n, int nmat, int m0, int 
     const int nbo = gje_outer_nb(n);
     const dim3 rg((n + 15) / 16, nmat), dg(nmat), t256(256), tdiag(kNsdDiagThreads), ig((n + 63) / 64, nmat);
     const int nt = (n + 63) / 64;
-    // 64-wide tiles from eight per CU on, as for k_gje_update: one matrix of 1500 (300
-    // of them) 1.45 ms in 64-wide and 1.38 in 32-wide tiles, four of 4000 (8064) 22.8 and 24.2
+    // 64-wide tiles from eight per CU on, as for k_gje_update; in 64- and in 32-wide ones:
+    // one matrix of 1500 (300 of them) 1.37 and 1.30 ms, one of 2500 (820) 3.27 and 2.97,
+    // four of 1500 (1200) 2.49 and 2.51, one of 3100 (1225) 4.61 and 4.60, one of 4000 (2016)
+    // 7.65 and 7.76, two of 3100 (2450) 6.91 and 7.18, four of 4000 (8064) 22.5 and 24.1
     const bool wide = (long long)nmat * nt * (nt + 1) / 2 >= 2000;
     for (int k = 0; k < n; k += nbo) {
         const int ke = std::min(n, k + nbo), K2 = k + kNsdNb;

@@ -735,7 +735,7 @@ __global__ __launch_bounds__(NT) void k_band_to_real3(const double2 *__restrict_
     }
 }
 
-// Two-pass band transform for cubic boxes of side N = 16, 24 or 32 (the
+// Two-pass band transform for cubic boxes of side N = 16, 24, 32 or 48 (the
 // inverse direction of the pair passes).
 // Pass X (k_band_x): lane = (band, box cell (iy, iz)).  The cell's x-stick
 // holds consecutive mx; each is placed at register mx mod N (zero elsewhere)

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(512, 4) void k_syrk_f64(const SyrkProb *__restrict_
 // the symmetric mirror.  A block takes 8 x 32 tiles on or above the diagonal: it
 // sums each element once, in rows, and writes the mirror in rows through LDS (read
 // where it lay, element by element down the columns, it took 0.62 ms at 1500 vectors
-// and six splits; 0.09 now).  In place (ns == 1, part == chi, no accumulation)
+// and six splits; 0.07 now).  In place (ns == 1, part == chi, no accumulation)
 // the same.  grid.y: output matrix.
 __global__ __launch_bounds__(256) void k_syrk_finalize(const SyrkFin *__restrict__ probs) {
     __shared__ double tile[kFinRows][kFinTile + 1];
