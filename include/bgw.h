@@ -207,7 +207,7 @@ typedef struct {
  * registers; the FP64 head rows of all vectors of a q in one pass over M;
  * one finalize launch.  The digits are scaled per column and run of 96
  * consecutive pairs (384 where the column's four runs are alike), so a value
- * counts to about 2^-40 of the largest of its run.  Output tiles and K-split counts per size class
+ * counts to 2^-36 of the largest of its run or better.  Output tiles and K-split counts per size class
  * (ng rounded up to 512, ceil(log2 K)) come from bgw_autotune when it has
  * run, from fixed rules otherwise.  Work is ordered on `stream`; calls on one
  * handle must not run concurrently (they share its workspace). */

@@ -942,7 +942,7 @@ static void launch_gje_update_t(double2 *A, int n, int nmat, int r0, int nbr, Gj
 // update: one matrix of 1500 (552) 7.19 and 6.76 ms, one of 2500 (1560) 24.76 and
 // 24.03, four of 1500 (2208) 8.79 and 8.46, one of 3100 (2303) 31.84 and 31.73, two of
 // 3100 (4606) 37.73 and 37.88, four of 4000 (15372) 83.0 and 86.2; the updates within
-// an outer block, of fewer columns, are in 32-wide tiles at all of these but the last.
+// an outer block, of fewer columns, are in 32-wide tiles at all of these.
 static void launch_gje_update(double2 *A, int n, int nmat, int r0, int nbr, GjeCols cs, const double2 *Rs,
                               hipStream_t st) {
     const long long t64 = (long long)((n + 63) / 64) * ((cs.count() + 63) / 64) * nmat;
