@@ -332,12 +332,13 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // [column][run]), eA - eB of its 64 rows (int8, [run][row]), eB of its rows and the
 // digit sums at the end of each run ([run][5][96] int32; of the last one at the
 // item's last k-step in it): chunk c in buffer c % 2, staged with the first
-// step that needs it and read where the sums start and end.  Every load to LDS
-// is one of a whole wave, 1 KB.
+// step that needs it and read where the sums start and end.  Every load to LDS is one
+// of a whole wave (masked ones at the end of two branches the compiler has merged
+// into one without their masks).
 constexpr int A_LDS = KSP * TR * 16;          // 32 KB
 constexpr int B_SLICE_LDS = TC * KSB;         // 6 KB
 constexpr int W_OFF = A_LDS + NSL * B_SLICE_LDS;
-constexpr int STG = W_OFF + 1024;             // 63 KB
+constexpr int STG = W_OFF + 256;              // 62.25 KB
 constexpr int EA_OFF = TC * NRUN * 2, EBR_OFF = EA_OFF + TR * NRUN, EC_OFF = EBR_OFF + 1024;
 constexpr int EC_RUN = NSL * TC * 4, EC_PIECES = (NRUN * EC_RUN + 1023) / 1024, E_LDS = EC_OFF + EC_PIECES * 1024;
 static_assert(EBR_OFF == 1024 && TR * NRUN * 2 <= 1024, "eB of the columns and eA - eB of the rows in one load");
@@ -379,8 +380,7 @@ struct StageSrc {
 // k-step (past K the last pair again: it meets zero digits of the other side);
 // B piece p = w + 8 i is slice p / 6, rows 16 (p % 6) .. +16 (past gpad,
 // where no sums are stored, the last ones again).  Wave 7 loads the
-// step's weights (two per lane, four times over; the vectors are padded by 128
-// entries) and wave 6 the exponents of the step's chunk when they are new.
+// step's weights (half a one per lane; the vectors are padded by 128 entries) and wave 6 the exponents of the step's chunk when they are new.
 __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, unsigned char *__restrict__ ebuf,
                                             const StageSrc &S, int x, bool first, int wave, int lane) {
     const long long t0 = (long long)x * KSP;
@@ -403,8 +403,8 @@ __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, u
                 (int)(S.b0 + (p / (TC / 16)) * S.b_slice + min(p % (TC / 16), S.b_last) * 1024), 0, 0);
     }
     if (wave == NWAVE - 1) {
-        __builtin_amdgcn_global_load_lds((const void *)(S.w + t0 + 2 * (lane & 15)), (lds_void_t *)(stage + W_OFF), 16, 0,
-                                         0);
+        __builtin_amdgcn_global_load_lds((const void *)((const char *)(S.w + t0) + 4 * lane),
+                                         (lds_void_t *)(stage + W_OFF), 4, 0, 0);
     } else if (wave == NWAVE - 2 && (first || x % NKS == 0)) {
         const int ch = x / NKS;
         int l = lane;
