@@ -378,9 +378,10 @@ struct StageSrc {
 
 // One k-step x into one stage.  A piece i of wave w is pair row 4w + i of the
 // k-step (past K the last pair again: it meets zero digits of the other side);
-// B piece p = w + 8 i is slice p / 6, rows 16 (p % 6) .. +16 (past gpad,
-// where no sums are stored, the last ones again).  Wave 7 loads the
-// step's weights (half a one per lane; the vectors are padded by 128 entries) and wave 6 the exponents of the step's chunk when they are new.
+// B piece p = w + 8 i is slice p / 6, rows 16 (p % 6) .. +16 (past gpad, where no sums
+// are stored, the last ones again).  Wave 7 loads the step's weights (half a one per
+// lane; the vectors are padded by 128 entries) and wave 6 the exponents of the step's
+// chunk when they are new.
 __device__ __forceinline__ void stage_issue(unsigned char *__restrict__ stage, unsigned char *__restrict__ ebuf,
                                             const StageSrc &S, int x, bool first, int wave, int lane) {
     const long long t0 = (long long)x * KSP;
@@ -595,7 +596,7 @@ __device__ __forceinline__ void split_step(const unsigned char *__restrict__ cur
 // the 32 weights into LDS with direct global->LDS loads, one step ahead
 // through two stages; each wave slices its 16 rows of w_t M_t(G) into
 // digits in registers and issues 90 MFMAs.
-// What bounds it (Ng = 4000, K = 40 960, four frequencies: 69.4 ms, 2.3 POPS;
+// What bounds it (Ng = 4000, K = 40 960, four frequencies: 69.1 ms, 2.3 POPS;
 // the BF16 form took 108.4): the MFMAs alone take 42.6 ms, at the 3.7 POPS
 // that the card holds on such data (4.7 on zeros: the clock falls with the
 // power); reading the fragments from LDS adds 7 ms, the barrier 3, the loads
