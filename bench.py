@@ -41,6 +41,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
 INT8_PEAK_TOPS = 5033.2  # dense
+# sources of the FP64 chi-sum and self-energy products (a traffic record holds for these)
+CHI_SOURCES = [f"paper_1111_4429_amd/csrc/{f}" for f in ("chi.hip", "f64_tile.h", "common.h")]
 SPLIT_PRODUCTS = 15  # INT8 digit products per FP64-equivalent product in the split form
 
 
@@ -304,7 +306,7 @@ def bench_kx(args, wl):
         name, work, peak = "k_chi_split (Kx, INT8 MFMA, 15 x 4 K^2 Ng)", SPLIT_PRODUCTS * flops, INT8_PEAK_TOPS
     nl = launches.get(key, 1)
     avg = per_step[key] / nl
-    kx_tr = load_traffic(f"herk_{wl.name}", ["paper_1111_4429_amd/csrc/chi.hip", "paper_1111_4429_amd/csrc/common.h"])
+    kx_tr = load_traffic(f"herk_{wl.name}", CHI_SOURCES)
     kx_traffic = kx_tr["bytes_per_launch"] if (kx_tr is not None and precision == bgw.FP64) else None
     ach = work / nl / (avg * 1e-3) / 1e12
     kx_ms = sum(per_step.get(k, 0) for k in ("weights", "herk", "finalize", "split_slice", "split_herk"))
@@ -425,7 +427,7 @@ def bench_sigma(args, wl, nouter=64):
     ch_ms = e0.elapsed_time(e1) / args.steps
     f_x = 4.0 * nouter * nouter * nocc * ng
     # HBM bytes of one Coulomb-hole call (all its kernels) from the committed PMC record
-    ch_tr = load_traffic(f"sigma-ch_{wl.name}", ["paper_1111_4429_amd/csrc/chi.hip", "paper_1111_4429_amd/csrc/common.h"])
+    ch_tr = load_traffic(f"sigma-ch_{wl.name}", CHI_SOURCES)
     f_w = lambda ni: 8.0 * ng * ng * ni * nouter + 8.0 * nouter * nouter * ni * ng
     flops = f_x + f_w(nocc) + f_w(ninner)
     out = {
@@ -656,8 +658,8 @@ def bench_realaxis(args, wl):
     work = SPLIT_PRODUCTS * flops if gemm == "split_herk" else flops
     peak = INT8_PEAK_TOPS if gemm == "split_herk" else FP64_PEAK_TFLOPS
     ach = work / nl / (g_ms * 1e-3) / 1e12
-    src = "split.hip" if gemm == "split_herk" else "chi.hip"
-    tr = load_traffic(f"{gemm}_{wl.name}", [f"paper_1111_4429_amd/csrc/{src}", "paper_1111_4429_amd/csrc/common.h"])
+    src = ["paper_1111_4429_amd/csrc/split.hip", "paper_1111_4429_amd/csrc/common.h"]
+    tr = load_traffic(f"{gemm}_{wl.name}", src if gemm == "split_herk" else CHI_SOURCES)
     # split against FP64 on four frequencies of the grid (both timed), and their difference
     pick = [0, nE // 3, 2 * nE // 3, nE - 1]
     cmp = {}
@@ -939,9 +941,10 @@ def main():
     src = {"pair": ["paper_1111_4429_amd/csrc/fft2.hip", "paper_1111_4429_amd/csrc/common.h"],
            "pair_x": ["paper_1111_4429_amd/csrc/fft2.hip", "paper_1111_4429_amd/csrc/common.h"],
            "band": ["paper_1111_4429_amd/csrc/fft2.hip", "paper_1111_4429_amd/csrc/common.h"],
-           "herk": ["paper_1111_4429_amd/csrc/chi.hip", "paper_1111_4429_amd/csrc/common.h"],
+           "herk": CHI_SOURCES,
            "split_herk": ["paper_1111_4429_amd/csrc/split.hip", "paper_1111_4429_amd/csrc/common.h"],
-           "invert": ["paper_1111_4429_amd/csrc/eps.hip", "paper_1111_4429_amd/csrc/common.h"]}[dominant]
+           "invert": ["paper_1111_4429_amd/csrc/eps.hip", "paper_1111_4429_amd/csrc/f64_tile.h",
+                      "paper_1111_4429_amd/csrc/common.h"]}[dominant]
     tr = load_traffic(f"{dominant}_{wl.name}", src)
     roof = {"kernel": name, "bound": bound, "achieved": ach, "peak": peak, "unit": unit, "frac": ach / peak,
             "traffic": None if tr is None else tr["bytes_per_launch"],

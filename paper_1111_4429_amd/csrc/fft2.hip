@@ -371,10 +371,10 @@ __global__ __launch_bounds__(NT) void k_pair_yz(const double2 *__restrict__ gv, 
 //   z: lane (plane p, iy) reads row Q[p][iy][.], does the N-point DFT in
 //      registers and writes the columns along x that hold sphere points to
 //      T[t][x][column] (iy fastest, so the stores of a wave are contiguous runs).
-// What bounds it on many pairs is memory: at 64 x 4 x 400 pairs of 1500 vectors
-// 11.5 GB read and 8.4 written at 4.2 TB/s (a large copy runs at 4.9), with the
-// box's corners, which hold no points, in T; without them (161 of 225 columns) the
-// pass took 4.99 -> 4.69 ms and pass B 2.26 -> 2.02.  Lines of 32 leave one wave per
+// What bounds it on many pairs is memory: at 64 x 4 x 400 pairs of 1500 vectors the L2s
+// read 23.4 GB (part of it from the last-level cache) and write 6.4, at 6.2 TB/s (a
+// large copy runs at 4.9).  T is without the box's corners, which hold no points (161
+// of 225 columns): the pass took 4.99 -> 4.69 ms and pass B 2.26 -> 2.02.  Lines of 32 leave one wave per
 // SIMD, which the masked stores held up (0.94 -> 1.15 ms for 64 x 128 pairs): there
 // T keeps the whole box (t_row then says so).
 // The Q row stride N + 1 is odd in 16-byte units, so both the column writes
